@@ -29,15 +29,25 @@ import workloads  # noqa: E402
 METRIC = "MLUPS and % HBM roofline (FP32 vs FP16-storage); adjoint/forward time ratio"
 HBM_PEAK_GBS = 8000.0
 ANALYSIS_CALLS = 5   # steady-state calls of the row averages and the droplet analysis
-# Algorithmic bytes per node update: the 27 populations read once and
-# written once (FP16 / BF16 deviations: 24 16-bit moving populations and 3
-# FP32 rest populations), plus one byte of solid flag when the lattice has
-# solid cells.
+# Algorithmic bytes per node update: the state read once and written once,
+# plus one byte of solid flag when the lattice has solid cells. FP64 and FP32
+# keep, at tau = tau_g = 1, the five moments of the pulled populations; else
+# the 27 populations (FP16 / BF16 deviations: 24 16-bit moving populations and
+# 3 FP32 rest populations).
 BYTES_PER_UPDATE = {"fp64": 432, "fp32": 216, "fp16dev": 120, "bf16dev": 120, "fix16dev": 108}
+MOMENT_BYTES_PER_UPDATE = {"fp64": 80, "fp32": 40}
 KERNEL_SOURCES = ("paper_2109_12565_amd/csrc/lb_kernels.hpp",
+                  "paper_2109_12565_amd/csrc/lb_moment.hpp",
                   "paper_2109_12565_amd/csrc/lb_step2.hpp",
                   "paper_2109_12565_amd/csrc/launch_impl.hpp",
                   "paper_2109_12565_amd/csrc/tlb.hip")
+
+
+def keeps_moments(w: dict, precision: str) -> bool:
+    """The library's choice of state for a workload (fused left at its default)."""
+    return (precision in MOMENT_BYTES_PER_UPDATE and w["params"]["tau"] == 1.0
+            and w["params"]["tau_g"] == 1.0
+            and 27 * w["lx"] * w["ly"] * (8 if precision == "fp64" else 4) < 0.99 * 2**32)
 
 
 def kernel_hash() -> str:
@@ -134,8 +144,8 @@ def adjoint_ratio(steps: int, ckpt: int, precision: str, config: str = "mid") ->
         sim.forward_taped(warm, ckpt)
         sim.adjoint(warm)
     # device memory of the tape (without row padding): at tau = tau_g = 1 the
-    # moments of every step (K = 1), or checkpoints, two segments' moments
-    # and two scratch states; else states
+    # moments of every step (K = 1), or checkpoints of moments and two
+    # segments' moments; else states
     elem = 8 if precision == "fp64" else 4
     state_bytes = 27 * w["lx"] * w["ly"] * elem
     moment_bytes = 5 * w["lx"] * w["ly"] * elem
@@ -148,7 +158,7 @@ def adjoint_ratio(steps: int, ckpt: int, precision: str, config: str = "mid") ->
         t_fwd, _ = timed(lambda: sim.step(steps))
     nck = -(-steps // ckpt)
     if tau_one:
-        tape = steps * moment_bytes if ckpt == 1 else (nck + 2) * state_bytes + 2 * ckpt * moment_bytes
+        tape = steps * moment_bytes if ckpt == 1 else (nck + 2 * ckpt) * moment_bytes
     else:
         tape = (nck + ckpt - 1) * state_bytes
     tape_gib = tape / 2**30
@@ -200,7 +210,8 @@ def precision_study(steps: int, every: int, storages) -> dict:
         e["mass_a_drift"] = (obs["mass_a"] - m0[pr]["mass_a"]) / m0[pr]["mass_a"]
         e["mass_b_drift"] = (obs["mass_b"] - m0[pr]["mass_b"]) / m0[pr]["mass_b"]
         info = sim.launch_info()
-        e["launch"] = ("fused two-step, %d lanes, %d-row chunks" % (info["fused_lanes"], info["fused_rows"])
+        e["launch"] = ("moment steps" if keeps_moments(w, pr) else
+                       "fused two-step, %d lanes, %d-row chunks" % (info["fused_lanes"], info["fused_rows"])
                        if info["fused_rows"] > 0 else "single steps")
         out["storages"][pr] = e
     out["wall_s"] = round(time.perf_counter() - t0, 1)
@@ -234,7 +245,7 @@ def companion_runs(config: str, precision: str) -> dict:
             launch = sim.launch_info()
         return {"workload": w["name"], "storage": prec, "steps": steps,
                 "mlups": round(w["lx"] * w["ly"] * steps / (ms * 1e-3) / 1e6, 1),
-                "ms_per_step": round(ms / steps, 4), "fused": launch["fused_rows"] > 0}
+                "ms_per_step": round(ms / steps, 4), "fused": launch["fused_rows"] > 0 and not keeps_moments(w, prec)}
 
     other = "fp16dev" if precision != "fp16dev" else "fp32"
     return {"other_storage": run(config, other, 300, 20),
@@ -344,9 +355,11 @@ def main() -> int:
     # stream (torch's current stream): tlb_step(n) with fused launches runs
     # (n - 1) // 2 of them and one or two single steps, so two calls whose
     # step counts differ by 2 (b - a) differ by exactly b - a fused launches;
-    # without the fused kernel they differ by that many single steps.
+    # without the fused kernel they differ by that many single steps (of the
+    # populations or the moments).
     launch = sim.launch_info()
-    fused = launch["fused_rows"] > 0
+    moments = keeps_moments(w, args.precision)
+    fused = launch["fused_rows"] > 0 and not moments
 
     def call_ms(n, reps=3):
         best = float("inf")
@@ -362,7 +375,8 @@ def main() -> int:
     ka, kb = 2, 12
     per_launch_s = (call_ms(2 * kb + 1) - call_ms(2 * ka + 1)) * 1e-3 / (2 * (kb - ka) if not fused
                                                                          else (kb - ka))
-    # the single step that ends every call (it also forms the observable sums)
+    # calls of one step (of the populations: the single step that ends every
+    # call and forms the observable sums)
     n_one = 20
     e3, e4 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
     e3.record(stream)
@@ -376,12 +390,14 @@ def main() -> int:
     n_single = args.steps - 2 * n_fused
     nodes = w["lx"] * w["ly"]
     mlups = nodes * args.steps / (total_ms * 1e-3) / 1e6
-    bpn = BYTES_PER_UPDATE[args.precision] + (1 if w["solid"] is not None else 0)
-    kernel, updates = ("lb_step2_kernel", 2) if n_fused > 0 else ("lb_step_kernel", 1)
+    bpn = ((MOMENT_BYTES_PER_UPDATE if moments else BYTES_PER_UPDATE)[args.precision]
+           + (1 if w["solid"] is not None else 0))
+    kernel, updates = (("lb_step2_kernel", 2) if n_fused > 0 else
+                       ("lb_moment_kernel" if moments else "lb_step_kernel", 1))
     if fused and n_fused == 0:  # fused kernel chosen, but too few steps to use it
         per_launch_s = single_s
-    # algorithmic bytes per launch: the method's bytes per lattice update
-    # (27 populations read and written once, plus the solid flag) times the
+    # algorithmic bytes per launch: the bytes per lattice update (the state
+    # read and written once, plus the solid flag) times the
     # updates one launch performs; the fused kernel moves its populations
     # once for two updates, so the bytes it must move per launch are half of
     # that (hbm_bytes_per_launch_min); `traffic` is the counted HBM rate
@@ -396,11 +412,13 @@ def main() -> int:
             "hbm_bytes_per_launch_min": bpn * nodes,
             "frac_of_min_bytes": round(moved / HBM_PEAK_GBS, 4),
             "launches": {"fused": n_fused, "single": n_single},
-            # what the counters show limits the kernel: the fused kernel does two
+            # what limits the kernel: the FP32 moment step the issue of its
+            # instructions, the FP64 one that and HBM; the fused kernel does two
             # steps' arithmetic per pass over HBM at 8 wavefronts per CU (LDS
             # caps it) and is bound by latency and instruction issue, as is the
             # 16-bit single step; the 4- and 8-byte single step by HBM
-            "limiter": "latency-issue" if n_fused > 0 or BYTES_PER_UPDATE[args.precision] <= 120
+            "limiter": "issue" if moments else
+                       "latency-issue" if n_fused > 0 or BYTES_PER_UPDATE[args.precision] <= 120
                        else "hbm"}
     traffic = measured_traffic(w["name"], args.precision, kernel)
     if traffic is not None:
@@ -431,7 +449,8 @@ def main() -> int:
         "achieved_over_copy": round(achieved / copy_gbs, 4),
         "traffic_over_copy": None if roof["traffic"] is None else round(roof["traffic"] / copy_gbs, 4)}
     single_gbs = bpn * nodes / single_s / 1e9
-    roof["single_step_kernel"] = {"kernel": "lb_step_kernel (with the observable sums)",
+    roof["single_step_kernel"] = {"kernel": "lb_moment_kernel" if moments else
+                                            "lb_step_kernel (with the observable sums)",
                                   "launch_us": round(single_s * 1e6, 2),
                                   "achieved": round(single_gbs, 1),
                                   "frac": round(single_gbs / HBM_PEAK_GBS, 4),

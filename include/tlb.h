@@ -79,8 +79,9 @@ enum tlb_launch_flags {
 
 /* tlb_params.fused: use of the fused two-step kernel (see tlb_step). */
 enum tlb_fused_mode {
-  TLB_FUSED_AUTO = 0,    /* where it pays (two blocks per CU: FP32, 16-bit) */
-  TLB_FUSED_NEVER = 1,
+  TLB_FUSED_AUTO = 0,    /* the library's choice: moment steps in FP64 and FP32
+                            (see tlb_step), else fused where it pays */
+  TLB_FUSED_NEVER = 1,   /* single population steps */
   TLB_FUSED_ALWAYS = 2   /* wherever it applies */
 };
 
@@ -114,8 +115,8 @@ typedef struct tlb_params {
   int32_t fused_rows;    /* rows per chunk of the fused kernel (1..4096), 0: chosen */
   int32_t fused_strip;   /* at most this many stored columns per fused strip
                             (1..245), 0: chosen */
-  int32_t rows;          /* rows per chunk of the single-step kernel (1..4096),
-                            0: chosen */
+  int32_t rows;          /* rows per chunk of the single-step kernel and of
+                            moment steps (1..4096), 0: chosen */
   int32_t fused_lanes;   /* lanes per block of the fused kernel, 128 or 256
                             (at most lanes - 10 stored columns per strip),
                             0: chosen */
@@ -168,8 +169,8 @@ int tlb_init(tlb_handle **out, const tlb_params *p, const double *rho_a,
 /* Device bytes of the workspace tlb_init_external needs for these
  * parameters and solid flags (host, ly*lx, or NULL): both population
  * buffers, the per-block observable partials, the observables, the bottom
- * temperature, the solid flags and the link masks, each part 256-byte
- * aligned. Queries the current device (the launch geometry depends on it).
+ * temperature, the solid flags, the link masks and the tile list of the
+ * moment steps, each part 256-byte aligned. Queries the current device (the launch geometry depends on it).
  * Returns the byte count, or TLB_EINVAL for invalid parameters. */
 int64_t tlb_workspace_bytes(const tlb_params *p, const uint8_t *solid);
 
@@ -190,18 +191,22 @@ int tlb_init_external(tlb_handle **out, const tlb_params *p, const double *rho_a
  * streaming with bounce-back / anti-bounce-back at solid links, moments,
  * forces, velocity shift (Eq. (6)) and BGK collision. Enqueues only. With
  * tau = tau_g = 1 (the collision then returns the equilibria of Eqs. (3),
- * (18)), pairs of steps may run as one fused launch where the handle's
- * storage and lattice allow it (see tlb_launch_info; flat walls at rest or
- * moving, posts allowed); the last step of a call is always a single step,
- * which also forms the observable sums of the new time, and results agree
- * with single steps to rounding. Returns TLB_EINVAL for nsteps < 0 or a
+ * (18)), FP64 and FP32 handles below 4 GiB of populations keep, with fused =
+ * TLB_FUSED_AUTO and no other fused option, the five moments rho_A, rho_B, j
+ * and T per node in place of the populations and advance those, one launch
+ * a step; the populations are formed where a call asks for them. Otherwise
+ * pairs of steps may run as one fused launch where the handle's storage and
+ * lattice allow it (see tlb_launch_info; flat walls at rest or moving, posts
+ * allowed); the last step of a call is then a single step, which also forms
+ * the observable sums of the new time. Results agree with single population
+ * steps to rounding either way. Returns TLB_EINVAL for nsteps < 0 or a
  * NULL handle, TLB_EDEVICE on a launch failure. */
 int tlb_step(tlb_handle *h, int64_t nsteps);
 
 /* Observables at the current time (synchronises the stream). After
- * tlb_init and tlb_step the sums are already on the device (formed by the
- * last step); after a taped run or a new bottom temperature the time level
- * is evaluated again. Returns TLB_ENUMERIC if a component mass is not
+ * population steps the sums are already on the device (formed by the last
+ * one); otherwise (moment steps, a taped run, a new bottom temperature) the
+ * time level is evaluated. Returns TLB_ENUMERIC if a component mass is not
  * finite. */
 int tlb_observables(tlb_handle *h, tlb_obs *out);
 
@@ -288,7 +293,8 @@ int tlb_set_bottom_temperature(tlb_handle *h, const double *t_bottom);
  * The tape (checkpoints) replaces any previous one and stays valid until the
  * next tlb_forward_taped, tlb_set_bottom_temperature or tlb_destroy; later
  * tlb_step calls do not touch it. Checkpoint memory is
- * ceil(nsteps / ckpt_every) copies of the state. ckpt_every = 1 keeps every
+ * ceil(nsteps / ckpt_every) copies of the state (populations, or the five
+ * moments where the handle keeps those). ckpt_every = 1 keeps every
  * step instead and the reverse sweep recomputes nothing: at tau = tau_g = 1
  * the steps write the moments rho_A, rho_B, j, T of their pulled state (5
  * values per node; the adjoint of a step at tau = 1 needs nothing else) and
@@ -318,10 +324,11 @@ int64_t tlb_time(const tlb_handle *h);
 /* Launch geometry chosen by tlb_init for the step kernels (Sec. 2.5 maps the
  * lattice onto GPU threads; here a block of `bx` threads marches over a
  * chunk of `rows` rows of a `bx`-column strip). fused_rows > 0 means that
- * tlb_step advances pairs of steps with the fused two-step kernel (tau =
- * tau_g = 1, flat walls at rest or moving; blocks of fused_lanes lanes,
- * strips of fused_strip stored columns, chunks of fused_rows rows); every
- * tlb_step call still ends with a single step. Host struct, written by the
+ * the fused two-step kernel applies (tau = tau_g = 1, flat walls at rest or
+ * moving; blocks of fused_lanes lanes, strips of fused_strip stored columns,
+ * chunks of fused_rows rows): tlb_step advances pairs of steps with it, ending
+ * each call with a single step, unless the handle advances moments (FP64 and
+ * FP32 with TLB_FUSED_AUTO, see tlb_step). Host struct, written by the
  * call. Returns TLB_EINVAL on a NULL argument. */
 typedef struct tlb_launch {
   int32_t bx, rows, grid_x, grid_y;

@@ -21,6 +21,11 @@ struct Geometry {
   int lanes2 = 256;  // lanes per block (kStep2Lanes or kStep2LanesNarrow)
   int strip2 = 0;    // stored columns per strip (lanes2 - kStep2Halo at most)
   dim3 grid2;
+  // moment state (tau = tau_g = 1, FP64 / FP32); rows_m == 0: not used
+  int rows_m = 0;    // rows per wavefront chunk
+  int strip_m = 0;   // stored columns per wavefront
+  dim3 grid_m;       // strips x chunks, one wavefront each
+  int slots_m = 0;   // wavefronts the chunks are cut for
 };
 
 // Lanes per block of the two-step kernel (wide and narrow blocks) and the
@@ -28,6 +33,8 @@ struct Geometry {
 constexpr int kStep2Lanes = 256;
 constexpr int kStep2LanesNarrow = 128;
 constexpr int kStep2Halo = 10;
+// Stored columns per wavefront of the moment kernel, at most.
+constexpr int kMomentStrip = 58;
 
 // Everything a launch needs from a handle.
 struct Device {
@@ -44,6 +51,11 @@ struct Device {
   const void* t_bottom = nullptr;  // compute-type copy of the bottom temperature
   double* partials = nullptr;
   double* fields = nullptr;
+  const void* tiles = nullptr;     // moment steps with solid cells: tlbk::MomentTile
+  int ntiles = 0, nlinked = 0;     // list, linked ones first
+  // FP32 moment step that a fused launch takes in a pair (see
+  // tlbk::kSameRounding): its first or its second step
+  bool pair_first = false, pair_second = false;
 };
 
 // Kernel passes of the step kernel.
@@ -68,6 +80,20 @@ enum class Pass {
   kStep2MomentsTopRow   // kStep2TopRow, and the moments of both steps
 };
 
+// Passes of the moment kernel (Geometry::rows_m > 0). Moment planes: rho_A,
+// rho_B, j_x, j_y, T of the pre-collision state, [5] planes of pop_stride
+// compute-type values.
+enum class MomentPass {
+  kStep,        // M(t) -> M(t+1)
+  kStepTopRow,  // same (flat walls at rest), and per strip the sum of T - t_top
+                // over the top row of time t+1 into Device::partials [strips]
+  kObserve,     // observable sums of time t into partials
+  kFields,      // fields of time t
+  kExport,      // f*(t) as doubles [27][ly][lx] into dst
+  kPost,        // f*(t) in the population layout into dst
+  kPostRest     // f(0) from M(0) in the population layout into dst
+};
+
 template <class St>
 struct Launcher {
   // Resident blocks per CU of the step kernel for this geometry.
@@ -83,6 +109,10 @@ struct Launcher {
   static void init_equilibrium(const Device& d, void* buf, const double* rho_a, const double* rho_b,
                                const double* temp, const double* ux0, const double* uy0);
   static void export_populations(const Device& d, const void* buf, double* out);
+  static void moment(const Device& d, MomentPass pass, const void* src, void* dst);
+  // M(0) from the initial fields (the velocities may be null).
+  static void init_moments(const Device& d, void* dst, const double* rho_a, const double* rho_b,
+                           const double* temp, const double* ux0, const double* uy0);
 };
 
 // Work buffers of the reverse sweep, in the compute type of the storage and

@@ -3,6 +3,7 @@
 
 #include "launch.hpp"
 #include "lb_kernels.hpp"
+#include "lb_moment.hpp"
 #include "lb_step2.hpp"
 
 namespace tlbh {
@@ -161,6 +162,89 @@ void launch_step2(const Device& d, const void* src, void* dst, Pass pass, void* 
   }
 }
 
+// Storages with the moment state: those whose populations are stored in the
+// compute type (the 16-bit ones round every stored population).
+template <class St>
+constexpr bool kHasMoments = !St::kFix && !St::kDev;
+
+template <class St, unsigned kMode>
+void launch_moment_kernel(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
+  constexpr bool kList = (kMode & tlbk::kMomStep) != 0 && (kMode & tlbk::kModeSolid) != 0;
+  hipLaunchKernelGGL((tlbk::lb_moment_kernel<St, kMode>), kList ? dim3(d.ntiles) : d.geo.grid_m,
+                     dim3(64), 0, d.stream, a);
+}
+
+// Passes that only read the time level: the walls' motion plays no part.
+template <class St, unsigned kMode>
+void launch_moment_solid(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
+  if (d.has_solid) launch_moment_kernel<St, kMode | tlbk::kModeSolid>(d, a);
+  else launch_moment_kernel<St, kMode>(d, a);
+}
+
+template <class St, unsigned kMode>
+void launch_moment_split(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
+  if constexpr (tlbk::kSameRounding<typename St::C>) {
+    if (d.pair_second) {
+      launch_moment_kernel<St, kMode | tlbk::kMomSplit>(d, a);
+      return;
+    }
+  }
+  launch_moment_kernel<St, kMode>(d, a);
+}
+
+template <class St>
+void launch_moment_step(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
+  constexpr unsigned M = tlbk::kMomStep, S = tlbk::kModeSolid, V = tlbk::kModeMoving;
+  if (d.moving) {
+    if (d.has_solid) launch_moment_split<St, M | S | V>(d, a);
+    else launch_moment_split<St, M | V>(d, a);
+  } else {
+    if (d.has_solid) launch_moment_split<St, M | S>(d, a);
+    else launch_moment_split<St, M>(d, a);
+  }
+}
+
+template <class St>
+void launch_moment(const Device& d, MomentPass pass, const void* src, void* dst) {
+  using namespace tlbk;
+  using C = typename St::C;
+  MomentArgs<C> a{};
+  a.s = make_args<C>(d, src, dst);
+  a.s.rows_per_block = d.geo.rows_m;
+  a.strip = d.geo.strip_m;
+  a.tiles = static_cast<const MomentTile*>(d.tiles);
+  a.ntiles = d.ntiles;
+  a.nlinked = d.nlinked;
+  // (the fused kernel without solid cells loads T_w, and with it 2 w T_w, in a
+  // block of its own at both levels, the one with solid cells at its second)
+  a.round_wall = d.pair_second || (d.pair_first && !d.has_solid);
+  a.out = static_cast<double*>(dst);
+  const tlb_params& p = *d.p;
+  // combined from the constants as the population kernels round them, so
+  // that both evaluate the same forces
+  auto w = [](int c2) { return (double)w_c2<C>(c2); };
+  auto q = [](int c2) { return (double)p_c2<C>(c2); };
+  for (int l = 0; l < 2; ++l) {
+    const double ga = (double)C(p.g_a[l]), gr = (double)C(p.g_r[l]);
+    a.g1[l] = C(ga * w(1) + gr * q(1));
+    a.g2[l] = C(ga * w(2) + gr * q(2));
+    a.g5[l] = C(gr * q(5));
+    a.h4[l] = C(2 * gr * q(4));
+    a.h5[l] = C(2 * gr * q(5));
+    a.h8[l] = C(2 * gr * q(8));
+  }
+  a.x2 = C((double)a.s.g12 * w(2) * (double)a.s.inv_rho0 * (double)a.s.inv_rho0);
+  switch (pass) {
+    case MomentPass::kStep: launch_moment_step<St>(d, a); break;
+    case MomentPass::kStepTopRow: launch_moment_split<St, kMomStep | kModeTopRow>(d, a); break;
+    case MomentPass::kObserve: launch_moment_solid<St, kMomObserve>(d, a); break;
+    case MomentPass::kFields: launch_moment_solid<St, kMomFields>(d, a); break;
+    case MomentPass::kExport: launch_moment_solid<St, kMomExport>(d, a); break;
+    case MomentPass::kPost: launch_moment_solid<St, kMomPost>(d, a); break;
+    case MomentPass::kPostRest: launch_moment_solid<St, kMomPost | kMomRest>(d, a); break;
+  }
+}
+
 template <class St, int BT, unsigned kMode>
 int step2_occupancy() {
   int n = 0;
@@ -247,6 +331,25 @@ void Launcher<St>::init_equilibrium(const Device& d, void* buf, const double* rh
   hipLaunchKernelGGL(tlbk::lb_init_equilibrium<St>, grid, dim3(256), 0, d.stream,
                      static_cast<typename St::T*>(buf), rho_a, rho_b, temp, ux0, uy0, d.solid, p.lx,
                      p.ly, d.pitch, d.pop_stride, C(p.rho_ref[0]), C(p.rho_ref[1]), C(p.t_ref));
+}
+
+template <class St>
+void Launcher<St>::moment(const Device& d, MomentPass pass, const void* src, void* dst) {
+  if constexpr (detail::kHasMoments<St>) detail::launch_moment<St>(d, pass, src, dst);
+}
+
+template <class St>
+void Launcher<St>::init_moments(const Device& d, void* dst, const double* rho_a,
+                                const double* rho_b, const double* temp, const double* ux0,
+                                const double* uy0) {
+  if constexpr (detail::kHasMoments<St>) {
+    using C = typename St::C;
+    const tlb_params& p = *d.p;
+    dim3 grid((p.lx + 255) / 256, p.ly, 1);
+    hipLaunchKernelGGL(tlbk::lb_moment_init<St>, grid, dim3(256), 0, d.stream,
+                       static_cast<C*>(dst), rho_a, rho_b, temp, ux0, uy0, d.solid, p.lx, d.pitch,
+                       d.pop_stride, C(p.rho_wall[0]), C(p.rho_wall[1]));
+  }
 }
 
 template <class St>

@@ -329,6 +329,16 @@ struct PopMem {
       __builtin_nontemporal_store(raw, reinterpret_cast<T*>(base + soff + voff));
     }
   }
+  // Store with the default cache policy (values the next launch reads while
+  // they are still in the caches), through the buffer resource.
+  __device__ void put(uint32_t soff, uint32_t voff, C v) const {
+    static_assert(kBuf, "32-bit offsets");
+    const T raw = St::encode(v);
+    if constexpr (sizeof(T) == 8)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, raw), rsrc, voff, soff, 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, raw), rsrc, voff, soff, 0);
+  }
 };
 
 // Bytes of a population buffer in units of one stored plane: 27 planes, and

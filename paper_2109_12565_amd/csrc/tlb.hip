@@ -17,6 +17,7 @@
 #include "droplets.hpp"
 #include "launch.hpp"
 #include "lb_kernels.hpp"
+#include "lb_moment.hpp"
 #include "lb_reduce.hpp"
 
 namespace {
@@ -42,6 +43,14 @@ struct tlb_handle {
   size_t elem = 0;                 // bytes per stored population value
   void* buf[2] = {nullptr, nullptr};
   int cur = 0;                     // buf[cur] = f*(t); buf[1-cur] = f*(t-1) or f(0)
+  // Moment state (launch.rows_m > 0): buf[1] holds the moments M(t) in slot
+  // `cur` (0 or 1), M(t-1) in slot 1 - cur, and in slot 2, when
+  // level_valid, M(t) pulled again under a bottom temperature set after the
+  // step (wall_changed); buf[0] is scratch for populations.
+  bool wall_changed = false;
+  bool level_valid = false;
+  tlbk::MomentTile* tiles = nullptr;  // moment steps with solid cells
+  int ntiles = 0, nlinked = 0;
   int64_t t = 0;
   bool has_solid = false;
   uint16_t* link = nullptr;
@@ -224,7 +233,98 @@ tlbh::Geometry choose_launch(const tlb_params& p, size_t buffer_bytes, bool soli
       l.grid2 = dim3((unsigned)strips2, (unsigned)((ly + l.rows2 - 1) / l.rows2), 1);
     }
   }
+
+  // Moment state: the library's own choice at tau = tau_g = 1 in FP64 and
+  // FP32 below 4 GiB (per step, moments / the launches it replaces, 4096 x
+  // 2048: FP32 127 / 263 us, FP64 178 / 677; 1024 x 512: 15.7 / 25.3, 17.8 /
+  // 52.2; 128 x 64: 6.1 / 12.0, 6.4 / 17.0). Any explicit choice of the fused
+  // kernel keeps that one.
+  const bool moments = tau_one && !l.wide && p.fused == TLB_FUSED_AUTO && p.fused_rows == 0 &&
+                       p.fused_strip == 0 && p.fused_lanes == 0 &&
+                       (p.precision == TLB_FP64 || p.precision == TLB_FP32);
+  if (moments) {
+    // A chunk costs its rows and about three more (two of equilibria, four of
+    // psi), so few tall chunks are best as long as every SIMD has its share:
+    // a lone wavefront of straight-line code already issues most of the time.
+    // Chunks for two wavefronts per SIMD; in FP64 (twice the time per row,
+    // all spent on issue) for one where that leaves at most 20 rows. Per step,
+    // chunks for one / two / three wavefronts per SIMD: FP32 512 x 256 8.7 /
+    // 9.5 / 10.3 us, 1024 x 512 16.1 / 15.0 / 16.8, 2048 x 512 24.2 / 23.1 /
+    // 24.3, 4096 x 2048 147 / 128 / 122; FP64 512 x 256 9.7 / 11.2 / 13.4,
+    // 1024 x 512 17.8 / 18.5 / 22.6, 2048 x 1024 - / 47.1 / 53.1.
+    constexpr long long kSimds = 4;
+    const long long strips_m = (lx + tlbh::kMomentStrip - 1) / tlbh::kMomentStrip;
+    auto rows_for = [&](long long waves) {
+      const long long chunks = std::max(1LL, cus * kSimds * waves / strips_m);
+      return (ly + chunks - 1) / chunks;
+    };
+    const bool one = p.precision == TLB_FP64 && rows_for(1) <= 20;
+    const long long rows_m = p.rows > 0 ? p.rows : rows_for(one ? 1 : 2);
+    l.rows_m = (int)std::min<long long>(rows_m, ly);
+    l.slots_m = (int)(cus * kSimds * (one ? 1 : 2));
+    l.strip_m = (int)((lx + strips_m - 1) / strips_m);
+    l.grid_m = dim3((unsigned)strips_m, (unsigned)((ly + l.rows_m - 1) / l.rows_m), 1);
+  }
   return l;
+}
+
+// Tiles of the moment step where solid cells exist. A row of a strip is
+// linked where a stored node's mask is not the flat walls' one; runs of linked
+// rows (with gaps of up to three others) are cut into tiles of half the
+// launch's chunk height (at most 8 rows: a linked row takes longer), the rest
+// into tiles of the chunk height, or the one at which all are resident at once.
+std::vector<tlbk::MomentTile> moment_tiles(const tlb_params& p, const tlbh::Geometry& g,
+                                           const std::vector<uint16_t>& link, int* nlinked) {
+  const int lx = p.lx, ly = p.ly;
+  const int strips = (int)g.grid_m.x;
+  std::vector<tlbk::MomentTile> linked, plain;
+  auto cut = [](std::vector<tlbk::MomentTile>& to, int strip, int y0, int y1, int most, int flag) {
+    const int n = (y1 - y0 + most - 1) / most;
+    for (int k = 0; k < n; ++k)
+      to.push_back({strip, y0 + (int)((long long)(y1 - y0) * k / n),
+                    y0 + (int)((long long)(y1 - y0) * (k + 1) / n), flag});
+  };
+  std::vector<tlbk::MomentTile> runs;  // of rows without links
+  std::vector<char> marked((size_t)ly);
+  for (int s = 0; s < strips; ++s) {
+    const int x0 = s * g.strip_m, x1 = std::min(x0 + g.strip_m, lx);
+    for (int y = 0; y < ly; ++y) {
+      const uint32_t flat = (y == 0 ? tlbk::kFromBelow : 0u) | (y == ly - 1 ? tlbk::kFromAbove : 0u);
+      const uint16_t* row = link.data() + (size_t)y * lx;
+      marked[y] = std::any_of(row + x0, row + x1, [&](uint16_t m) { return m != flat; });
+    }
+    for (int y = 0; y < ly;) {
+      int e = y;
+      if (marked[y]) {
+        for (int k = y; k < ly && k < e + 4; ++k)
+          if (marked[k]) e = k + 1;
+        cut(linked, s, y, e, std::min(8, std::max(1, g.rows_m / 2)), 1);
+      } else {
+        while (e < ly && !marked[e]) ++e;
+        runs.push_back({s, y, e, 0});
+      }
+      y = e;
+    }
+  }
+  int rows = g.rows_m;
+  if (p.rows == 0) {
+    const long long room = std::max<long long>(1, g.slots_m - (long long)linked.size());
+    auto count = [&](int h) {
+      long long n = 0;
+      for (const auto& t : runs) n += (t.y1 - t.y0 + h - 1) / h;
+      return n;
+    };
+    while (rows < ly && count(rows) > std::max<long long>(room, (long long)runs.size())) ++rows;
+  }
+  for (const auto& t : runs) cut(plain, t.strip, t.y0, t.y1, rows, 0);
+  // strip fastest: neighbouring strips at the same height run together
+  std::stable_sort(plain.begin(), plain.end(),
+                   [](const auto& u, const auto& v) { return u.y0 < v.y0; });
+  std::stable_sort(linked.begin(), linked.end(),
+                   [](const auto& u, const auto& v) { return u.y0 < v.y0; });
+  *nlinked = (int)linked.size();
+  linked.insert(linked.end(), plain.begin(), plain.end());
+  return linked;
 }
 
 tlbh::Device device_view(const tlb_handle* h, double* fields = nullptr,
@@ -243,6 +343,9 @@ tlbh::Device device_view(const tlb_handle* h, double* fields = nullptr,
   d.t_bottom = h->t_bottom;
   d.partials = partials ? partials : h->partials;
   d.fields = fields ? fields : h->fields;
+  d.tiles = h->tiles;
+  d.ntiles = h->ntiles;
+  d.nlinked = h->nlinked;
   return d;
 }
 
@@ -253,14 +356,76 @@ void launch_pass(const tlb_handle* h, tlbh::Pass pass, const void* src, void* ds
                [&](auto st) { tlbh::Launcher<decltype(st)>::step(d, pass, src, dst, moments); });
 }
 
+// Bytes of one set of moments: rho_A, rho_B, j_x, j_y, T of every node in the
+// compute type (a slot of the moment state and of the adjoint's moment tape).
+size_t moment_bytes(const tlb_handle* h) {
+  return (size_t)5 * h->pop_stride * (h->p.precision == TLB_FP64 ? sizeof(double) : sizeof(float));
+}
+
+bool has_moments(const tlb_handle* h) { return h->launch.rows_m > 0; }
+
+// Slot k of the moment state (buf[1] holds five).
+void* moment_slot(const tlb_handle* h, int k) {
+  return static_cast<char*>(h->buf[1]) + (size_t)k * moment_bytes(h);
+}
+
+// Step s of a run of n: fused launches take pairs while three steps remain.
+void set_pair(tlbh::Device* d, int64_t s, int64_t n) {
+  d->pair_first = s % 2 == 0 && s + 2 < n;
+  d->pair_second = s % 2 == 1 && s + 1 < n;
+}
+
+void launch_moment(const tlb_handle* h, tlbh::MomentPass pass, const void* src, void* dst,
+                   double* fields = nullptr, double* partials = nullptr, int64_t step = 0,
+                   int64_t nsteps = 0) {
+  tlbh::Device d = device_view(h, fields, partials);
+  set_pair(&d, step, nsteps);
+  with_storage(h->p.precision,
+               [&](auto st) { tlbh::Launcher<decltype(st)>::moment(d, pass, src, dst); });
+}
+
+// Step s of a run of n of the moment state.
+void moment_step(tlb_handle* h, int64_t s, int64_t n) {
+  launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, h->cur), moment_slot(h, 1 - h->cur),
+                nullptr, nullptr, s, n);
+  h->cur = 1 - h->cur;
+  h->t += 1;
+}
+
+// The moments that observables and fields of time t are formed from: the
+// state's, or, after a new bottom temperature, those of the same step pulled
+// under it.
+const void* observed_moments(tlb_handle* h) {
+  if (!h->wall_changed || h->t == 0) return moment_slot(h, h->cur);
+  if (!h->level_valid)  // (a run's last step, never the second of a pair)
+    launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, 1 - h->cur), moment_slot(h, 2));
+  h->level_valid = true;
+  return moment_slot(h, 2);
+}
+
 // Re-run the step that produced f*(t) without storing, to evaluate the
-// moments, forces and u^H of time t (observables or fields).
+// moments, forces and u^H of time t (observables or fields). The moment
+// state has the moments of time t at hand; only the stress needs the pulled
+// populations, from f*(t-1) (or f(0)) rebuilt in buf[0].
 enum class Level { kObserve, kFields, kStress };
 
 int evaluate_time_level(tlb_handle* h, Level what, double* fields = nullptr) {
   const void* src = h->buf[1 - h->cur];
   using tlbh::Pass;
   const bool init = h->t == 0;
+  if (has_moments(h)) {
+    using tlbh::MomentPass;
+    if (what == Level::kStress) {
+      launch_moment(h, init ? MomentPass::kPostRest : MomentPass::kPost,
+                    moment_slot(h, init ? h->cur : 1 - h->cur), h->buf[0]);
+      launch_pass(h, init ? Pass::kStressInit : Pass::kStress, h->buf[0], nullptr, fields);
+    } else {
+      launch_moment(h, what == Level::kFields ? MomentPass::kFields : MomentPass::kObserve,
+                    observed_moments(h), nullptr, fields);
+    }
+    TLB_HIP(h, hipGetLastError());
+    return TLB_OK;
+  }
   Pass pass = init ? Pass::kObserveInit : Pass::kObserve;
   if (what == Level::kFields) pass = init ? Pass::kFieldsInit : Pass::kFields;
   if (what == Level::kStress) pass = init ? Pass::kStressInit : Pass::kStress;
@@ -302,10 +467,9 @@ size_t state_bytes(const tlb_handle* h) {
   return buffer_planes(h->p.precision) * h->pop_stride * h->elem;
 }
 
-// Bytes of one moment-tape slot: rho_A, rho_B, j_x, j_y, T of every node in
-// the compute type (the adjoint's storages: FP64, FP32).
-size_t moment_bytes(const tlb_handle* h) {
-  return (size_t)5 * h->pop_stride * (h->p.precision == TLB_FP64 ? sizeof(double) : sizeof(float));
+// Bytes of a checkpoint of the taped run: the moment state or the populations.
+size_t checkpoint_bytes(const tlb_handle* h) {
+  return has_moments(h) ? moment_bytes(h) : state_bytes(h);
 }
 
 // Device buffer of at least `bytes`, reallocated when too small.
@@ -327,9 +491,11 @@ int ensure_buffer(tlb_handle* h, void** ptr, size_t* cap, size_t bytes, const ch
   return TLB_OK;
 }
 
-// Slots per step of the taped run's loss terms: one per strip of the fused
-// kernel (whose launches write per-strip top-row sums), else one.
+// Slots per step of the taped run's loss terms: one per strip of the moment
+// kernel or of the fused kernel (whose launches write per-strip top-row
+// sums), else one.
 int loss_stride(const tlb_handle* h) {
+  if (has_moments(h)) return (int)h->launch.grid_m.x;
   return h->launch.rows2 > 0 ? (int)h->launch.grid2.x : 1;
 }
 
@@ -555,12 +721,14 @@ int check_params(const tlb_params* p) {
 
 // Layout of the step path's device buffers (each part 256-byte aligned):
 // both population buffers, the per-block observable partials, the
-// observables, the bottom temperature, the solid flags and the link masks.
+// observables, the bottom temperature, the solid flags, the link masks and
+// the tile list.
 struct Workspace {
-  size_t buf = 0, partials = 0, obs = 0, t_bottom = 0, solid = 0, link = 0, total = 0;
+  size_t buf = 0, partials = 0, obs = 0, t_bottom = 0, solid = 0, link = 0, tiles = 0, total = 0;
 };
 
-Workspace workspace_layout(const tlb_params& p, size_t state_b, size_t nblocks) {
+Workspace workspace_layout(const tlb_params& p, size_t state_b, size_t nblocks,
+                           const tlbh::Geometry& g, bool has_solid) {
   const size_t n = (size_t)p.lx * p.ly;
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   Workspace w;
@@ -570,8 +738,19 @@ Workspace workspace_layout(const tlb_params& p, size_t state_b, size_t nblocks) 
   w.t_bottom = w.obs + up(8 * sizeof(double));
   w.solid = w.t_bottom + up((size_t)p.lx * sizeof(double));
   w.link = w.solid + up(n);
-  w.total = w.link + up(n * sizeof(uint16_t));
+  w.tiles = w.link + up(n * sizeof(uint16_t));
+  // at most one tile per strip and row
+  w.total = w.tiles + (has_solid && g.rows_m > 0
+                           ? up((size_t)g.grid_m.x * p.ly * sizeof(tlbk::MomentTile))
+                           : 0);
   return w;
+}
+
+// Blocks that write observable partials: of the step kernel, or wavefronts of
+// the moment kernel.
+size_t partial_blocks(const tlbh::Geometry& g) {
+  return std::max((size_t)g.grid.x * g.grid.y,
+                  g.rows_m > 0 ? (size_t)g.grid_m.x * g.grid_m.y : (size_t)0);
 }
 
 bool any_solid(const uint8_t* solid, size_t n) {
@@ -679,9 +858,19 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
   } while (0)
 
   const size_t buf_bytes = state_bytes(h);
-  const size_t nblocks = (size_t)h->launch.grid.x * h->launch.grid.y;
+  const size_t nblocks = partial_blocks(h->launch);
+  std::vector<tlbk::MomentTile> tiles;
+  if (has_moments(h) && h->has_solid) {
+    try {
+      tiles = moment_tiles(*p, h->launch, link, &h->nlinked);
+    } catch (const std::bad_alloc&) {
+      fail(nullptr, TLB_ENOMEM, "tlb_init: host allocation failed");
+      return cleanup_fail(TLB_ENOMEM);
+    }
+    h->ntiles = (int)tiles.size();
+  }
   if (workspace) {
-    const Workspace ws = workspace_layout(*p, buf_bytes, nblocks);
+    const Workspace ws = workspace_layout(*p, buf_bytes, nblocks, h->launch, h->has_solid);
     if (workspace_bytes < ws.total) {
       fail(nullptr, TLB_EINVAL, "tlb_init_external: workspace of %zu bytes, %zu needed",
            workspace_bytes, ws.total);
@@ -696,6 +885,7 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
     h->t_bottom = base + ws.t_bottom;
     h->solid = reinterpret_cast<uint8_t*>(base + ws.solid);
     if (h->has_solid) h->link = reinterpret_cast<uint16_t*>(base + ws.link);
+    if (!tiles.empty()) h->tiles = reinterpret_cast<tlbk::MomentTile*>(base + ws.tiles);
   } else {
     INIT_HIP(hipMalloc(&h->buf[0], buf_bytes));
     INIT_HIP(hipMalloc(&h->buf[1], buf_bytes));
@@ -704,12 +894,16 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
     INIT_HIP(hipMalloc(&h->t_bottom, lx * (is_fp64(h) ? sizeof(double) : sizeof(float))));
     INIT_HIP(hipMalloc(&h->solid, n));
     if (h->has_solid) INIT_HIP(hipMalloc(&h->link, n * sizeof(uint16_t)));
+    if (!tiles.empty()) INIT_HIP(hipMalloc(&h->tiles, tiles.size() * sizeof(tiles[0])));
   }
   INIT_HIP(hipMemsetAsync(h->buf[1], 0, buf_bytes, h->stream));
   INIT_HIP(hipMemcpyAsync(h->solid, sol.data(), n, hipMemcpyHostToDevice, h->stream));
   if (h->has_solid)
     INIT_HIP(hipMemcpyAsync(h->link, link.data(), n * sizeof(uint16_t), hipMemcpyHostToDevice,
                             h->stream));
+  if (!tiles.empty())
+    INIT_HIP(hipMemcpyAsync(h->tiles, tiles.data(), tiles.size() * sizeof(tiles[0]),
+                            hipMemcpyHostToDevice, h->stream));
   rc = tlb_set_bottom_temperature(h, t_bottom);
   if (rc != TLB_OK) {
     snprintf(g_init_error, sizeof g_init_error, "%s", h->err);
@@ -717,7 +911,7 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
   }
 
   // initial fields (staged in buf[0], which holds at least 40 bytes per
-  // node) -> f(0) in buf[1] -> f*(0) in buf[0]
+  // node) -> f(0) in buf[1] -> f*(0) in buf[0], or -> M(0)
   double* d_fields = static_cast<double*>(h->buf[0]);
   const int nf = (ux0 && uy0) ? 5 : 3;
   const double* srcs[5] = {rho_a, rho_b, temp, ux0, uy0};
@@ -726,18 +920,21 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
                             h->stream));
   const double* dux = nf == 5 ? d_fields + 3 * n : nullptr;
   const double* duy = nf == 5 ? d_fields + 4 * n : nullptr;
-  {
-    const tlbh::Device d = device_view(h);
-    with_storage(p->precision, [&](auto st) {
-      tlbh::Launcher<decltype(st)>::init_equilibrium(d, h->buf[1], d_fields, d_fields + n,
-                                                     d_fields + 2 * n, dux, duy);
-    });
+  const tlbh::Device d = device_view(h);
+  with_storage(p->precision, [&](auto st) {
+    using L = tlbh::Launcher<decltype(st)>;
+    if (has_moments(h))
+      L::init_moments(d, moment_slot(h, 0), d_fields, d_fields + n, d_fields + 2 * n, dux, duy);
+    else
+      L::init_equilibrium(d, h->buf[1], d_fields, d_fields + n, d_fields + 2 * n, dux, duy);
+  });
+  INIT_HIP(hipGetLastError());
+  if (!has_moments(h)) {
+    INIT_HIP(hipMemsetAsync(h->buf[0], 0, buf_bytes, h->stream));
+    launch_pass(h, tlbh::Pass::kInitStep, h->buf[1], h->buf[0]);
+    INIT_HIP(hipGetLastError());
+    h->obs_t = 0;
   }
-  INIT_HIP(hipGetLastError());
-  INIT_HIP(hipMemsetAsync(h->buf[0], 0, buf_bytes, h->stream));
-  launch_pass(h, tlbh::Pass::kInitStep, h->buf[1], h->buf[0]);
-  INIT_HIP(hipGetLastError());
-  h->obs_t = 0;
   INIT_HIP(hipStreamSynchronize(h->stream));
 #undef INIT_HIP
   h->cur = 0;
@@ -780,12 +977,18 @@ int64_t tlb_workspace_bytes(const tlb_params* p, const uint8_t* solid) {
                          storage_bytes(p->precision);
   const bool tau_one = p->tau == 1.0 && p->tau_g == 1.0 && !(p->launch_flags & TLB_LAUNCH_GENERAL_PATH);
   const tlbh::Geometry g = choose_launch(*p, state_b, has_solid, tau_one);
-  return (int64_t)workspace_layout(*p, state_b, (size_t)g.grid.x * g.grid.y).total;
+  return (int64_t)workspace_layout(*p, state_b, partial_blocks(g), g, has_solid).total;
 }
 
 int tlb_step(tlb_handle* h, int64_t nsteps) {
   if (!h) return fail(nullptr, TLB_EINVAL, "tlb_step: NULL handle");
   if (nsteps < 0) return fail(h, TLB_EINVAL, "tlb_step: nsteps < 0");
+  if (has_moments(h)) {
+    for (int64_t s = 0; s < nsteps; ++s) moment_step(h, s, nsteps);
+    if (nsteps > 0) h->wall_changed = h->level_valid = false;
+    TLB_HIP(h, hipGetLastError());
+    return TLB_OK;
+  }
   // Fused two-step launches first; the call always ends with a single step,
   // so the other buffer holds f*(t-1), from which fields and stress of
   // time t are pulled. That last step also leaves the observable sums of
@@ -827,8 +1030,9 @@ int tlb_launch_info(const tlb_handle* h, tlb_launch* out) {
 
 int tlb_observables(tlb_handle* h, tlb_obs* out) {
   if (!h || !out) return fail(h, TLB_EINVAL, "tlb_observables: NULL argument");
-  // the last step of tlb_step left the sums of the current time; otherwise
-  // (a taped run, a new bottom temperature) re-evaluate the time level
+  // the last population step of tlb_step left the sums of the current time;
+  // otherwise (the moment state, a taped run, a new bottom temperature)
+  // evaluate the time level
   if (h->obs_t != h->t) {
     int rc = evaluate_time_level(h, Level::kObserve);
     if (rc != TLB_OK) return rc;
@@ -836,7 +1040,8 @@ int tlb_observables(tlb_handle* h, tlb_obs* out) {
   }
   tlbk::ObsArgs oa{};
   oa.partials = h->partials;
-  oa.nblocks = (int)(h->launch.grid.x * h->launch.grid.y);
+  const dim3& g = has_moments(h) ? h->launch.grid_m : h->launch.grid;
+  oa.nblocks = (int)(g.x * g.y);
   oa.n_fluid = h->n_fluid;
   oa.n_top = h->n_top;
   oa.kappa = (h->p.tau_g - 0.5) / 3.0;
@@ -977,7 +1182,9 @@ int tlb_get_populations(tlb_handle* h, double* out) {
   const int lx = h->p.lx, ly = h->p.ly;
   const size_t total = (size_t)27 * lx * ly;
   if (!h->export_buf) TLB_HIP(h, hipMalloc(&h->export_buf, total * sizeof(double)));
-  {
+  if (has_moments(h)) {
+    launch_moment(h, tlbh::MomentPass::kExport, moment_slot(h, h->cur), h->export_buf);
+  } else {
     const tlbh::Device d = device_view(h);
     with_storage(h->p.precision, [&](auto st) {
       tlbh::Launcher<decltype(st)>::export_populations(d, h->buf[h->cur], h->export_buf);
@@ -995,6 +1202,8 @@ int tlb_set_bottom_temperature(tlb_handle* h, const double* t_bottom) {
   const int lx = h->p.lx;
   h->tape_valid = false;
   h->obs_t = -1;
+  h->wall_changed = true;
+  h->level_valid = false;
   h->host_tb.assign(t_bottom, t_bottom + lx);
   h->dtdy_sum = dtdy_sum(h);
   if (is_fp64(h)) {
@@ -1039,7 +1248,7 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
     if ((double)nsteps * per_step <= budget) {
       ckpt_every = 1;
     } else {
-      const double k = std::ceil((double)nsteps * (double)sb / budget);
+      const double k = std::ceil((double)nsteps * (double)checkpoint_bytes(h) / budget);
       ckpt_every = (int32_t)std::min<double>(std::max(2.0, k), (double)std::max<int64_t>(nsteps, 2));
     }
   }
@@ -1049,7 +1258,8 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
   // ckpt_every steps and each segment's moments recomputed in the sweep.
   const bool moment_tape = h->tau_one && ckpt_every == 1;
   const int64_t nck = moment_tape ? 0 : (nsteps + ckpt_every - 1) / ckpt_every;
-  int rc = nck > 0 ? ensure_buffer(h, &h->ckpt, &h->ckpt_cap, (size_t)nck * sb, "checkpoints")
+  int rc = nck > 0 ? ensure_buffer(h, &h->ckpt, &h->ckpt_cap, (size_t)nck * checkpoint_bytes(h),
+                                        "checkpoints")
                    : TLB_OK;
   if (rc == TLB_OK && moment_tape)
     rc = ensure_buffer(h, &h->mtape, &h->mtape_cap, (size_t)nsteps * moment_bytes(h),
@@ -1075,7 +1285,30 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
     h->cur = 1 - h->cur;
     h->t += n;
   };
-  if (moment_tape) {
+  if (has_moments(h)) {
+    // The steps write the moments of each time level where they stay: into
+    // its tape slot (ckpt_every = 1) or, at a checkpoint, into that; the last
+    // two levels also go to the handle's slots.
+    const size_t mb = moment_bytes(h);
+    auto copy = [&](void* dst, const void* src) {
+      return hipMemcpyAsync(dst, src, mb, hipMemcpyDeviceToDevice, h->stream);
+    };
+    auto ckpt = [&](int64_t k) { return static_cast<char*>(h->ckpt) + (size_t)(k / ckpt_every) * mb; };
+    const void* src = moment_slot(h, h->cur);   // M(t0 + k)
+    if (!moment_tape) TLB_HIP(h, copy(ckpt(0), src));
+    for (int64_t k = 0; k < nsteps; ++k) {
+      void* own = moment_slot(h, 1 - h->cur);
+      void* dst = own;
+      if (moment_tape) dst = static_cast<char*>(h->mtape) + (size_t)k * mb;
+      else if (k + 1 < nsteps && (k + 1) % ckpt_every == 0) dst = ckpt(k + 1);
+      launch_moment(h, tlbh::MomentPass::kStepTopRow, src, dst, nullptr,
+                    w.loss_terms + (size_t)k * stride, k, nsteps);
+      if (dst != own && k + 2 >= nsteps) TLB_HIP(h, copy(own, dst));
+      src = dst;
+      advance(1);
+    }
+    h->wall_changed = h->level_valid = false;
+  } else if (moment_tape) {
     auto mslot = [&](int64_t k) { return static_cast<char*>(h->mtape) + (size_t)k * moment_bytes(h); };
     int64_t k = 0;
     for (; fused && k + 2 < nsteps; k += 2) {
@@ -1107,7 +1340,7 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
     h->cur = 1 - h->cur;
     h->t += nsteps;
   }
-  for (int64_t k = 0; ckpt_every > 1 && k < nsteps;) {
+  for (int64_t k = 0; !has_moments(h) && ckpt_every > 1 && k < nsteps;) {
     if (k % ckpt_every == 0)
       TLB_HIP(h, hipMemcpyAsync(static_cast<char*>(h->ckpt) + (size_t)(k / ckpt_every) * sb,
                                 h->buf[h->cur], sb, hipMemcpyDeviceToDevice, h->stream));
@@ -1154,7 +1387,7 @@ int tlb_adjoint_step(tlb_handle* h, int64_t nsteps, double seed, double* grad_t_
   const bool moments = h->tau_one;
   int rc = TLB_OK;
   if (moments && K > 1) {
-    rc = ensure_buffer(h, &h->tape, &h->tape_cap, 2 * sb, "tape");
+    if (!has_moments(h)) rc = ensure_buffer(h, &h->tape, &h->tape_cap, 2 * sb, "tape");
     if (rc == TLB_OK)
       rc = ensure_buffer(h, &h->mtape, &h->mtape_cap, 2 * (size_t)K * mb, "moment tape");
     if (rc == TLB_OK && !h->side) {
@@ -1199,7 +1432,17 @@ int tlb_adjoint_step(tlb_handle* h, int64_t nsteps, double seed, double* grad_t_
   };
   auto recompute = [&](int64_t seg) {
     const int len = (int)std::min<int64_t>(K, nsteps - seg * K);
-    const void* src = static_cast<char*>(h->ckpt) + (size_t)seg * sb;
+    const void* src = static_cast<char*>(h->ckpt) + (size_t)seg * checkpoint_bytes(h);
+    if (has_moments(h)) {
+      for (int j = 0; j < len; ++j) {
+        set_pair(&side, seg * K + j, nsteps);
+        with_adjoint_storage(h, [&](auto st) {
+          tlbh::Launcher<decltype(st)>::moment(side, tlbh::MomentPass::kStep, src, mseg(seg, j));
+        });
+        src = mseg(seg, j);
+      }
+      return;
+    }
     int b = 0;
     for (int j = 0; j < len;) {
       void* dst = static_cast<char*>(h->tape) + (size_t)b * sb;
@@ -1279,12 +1522,14 @@ int tlb_destroy(tlb_handle* h) {
     h->buf[0] = h->buf[1] = h->t_bottom = nullptr;
     h->link = nullptr;
     h->solid = nullptr;
+    h->tiles = nullptr;
     h->partials = h->obs = nullptr;
   }
   void* ptrs[] = {h->buf[0],   h->buf[1],     h->link,       h->solid,      h->t_bottom,
                   h->partials, h->obs,        h->fields,     h->rows,       h->export_buf,
                   h->ckpt,     h->tape,       h->mtape,      h->adj,        h->adj_scalars,
-                  h->drop_nodes, h->drop_tiles, h->drop_error, h->drop_tb,  h->drop_acc};
+                  h->drop_nodes, h->drop_tiles, h->drop_error, h->drop_tb,  h->drop_acc,
+                  h->tiles};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   for (hipEvent_t e : h->ev_side)

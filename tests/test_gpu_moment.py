@@ -1,0 +1,168 @@
+"""The moment state (tau = tau_g = 1, FP64 / FP32, the library's own choice)
+against runs of population steps (fused = "never") and against the oracle.
+
+Both advance the same scheme; they differ in the order of sums and in the
+contraction of multiply-adds. Bars as for the fused kernel against single
+steps: 1e-13 in FP64 after 18 steps, 2e-6 in FP32 (2e-5 of max|u| for
+velocities), 1e-12 against the oracle after 150 steps. Lattices around the
+widths where a wavefront's 58 stored columns end, narrower than its halo, and
+with one to a few rows.
+"""
+import numpy as np
+import pytest
+
+import workloads
+from oracle.oracle import ModelParams, Oracle
+from paper_2109_12565_amd import Simulation
+
+from test_gpu_parity import field_errors, pop_errors, posts_case, rel
+from test_gpu_step2 import CASES, assert_close_state, droplet_case
+
+pytestmark = pytest.mark.gpu
+
+U_WALL = (-0.01, 0.02)
+
+
+def make(case, precision, fused="auto", **extra):
+    return Simulation(dict(case["params"], **extra), case["rho_a"], case["rho_b"], case["temp"],
+                      solid=case.get("solid"), t_bottom=case.get("t_bottom"), precision=precision,
+                      launch={"fused": fused})
+
+
+def bars(precision):
+    return (1e-13, 1e-13) if precision == "fp64" else (2e-6, 2e-5)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("name", sorted(CASES))
+@pytest.mark.parametrize("u_wall", [(0.0, 0.0), U_WALL])
+def test_moment_steps_match_population_steps(precision, name, u_wall):
+    case = CASES[name]()
+    print(name, precision, u_wall, flush=True)
+    a, b = (make(case, precision, f, u_wall=u_wall) for f in ("auto", "never"))
+    assert_close_state(a, b, *bars(precision))   # t = 0
+    for n in (9, 1, 2, 6):
+        a.step(n)
+        b.step(n)
+    assert a.t == b.t == 18
+    assert_close_state(a, b, *bars(precision))
+
+
+@pytest.mark.parametrize("lx,ly", [(1, 1), (2, 5), (5, 3), (64, 1), (7, 2), (58, 9), (59, 4), (116, 30),
+                                   (117, 7), (175, 13)])
+def test_moment_edge_shapes_fp64(lx, ly):
+    """Velocities get 1e-11 of max|u|, which is small on these lattices."""
+    case = droplet_case(lx, ly, seed=lx + ly)
+    a, b = (make(case, "fp64", f) for f in ("auto", "never"))
+    for n in (7, 4):
+        a.step(n)
+        b.step(n)
+    assert_close_state(a, b, 1e-13, 1e-11)
+
+
+def test_moment_state_matches_oracle_with_posts_and_moving_walls():
+    case = posts_case()
+    sim = make(case, "fp64", u_wall=U_WALL)
+    ora = Oracle(ModelParams(**dict(case["params"], u_wall=U_WALL)), case["rho_a"], case["rho_b"],
+                 case["temp"], solid=case["solid"], t_bottom=case["t_bottom"])
+    sim.step(151)
+    ora.step(151)
+    errs = field_errors(sim.fields(), ora.fields())
+    assert max(errs.values()) <= 1e-12, errs
+    perr = pop_errors(sim.populations(), ora.post_collision())
+    assert max(perr.values()) <= 1e-12, perr
+
+
+@pytest.mark.parametrize("name", ["small", "posts"])
+def test_new_bottom_temperature_between_steps(name):
+    """A new bottom temperature enters the observables, fields and stress of
+    the current time at once (its wall links are pulled again), leaves the
+    populations, and enters the steps that follow; also twice, and with a
+    velocity start at t = 0."""
+    case = CASES[name]()
+    shape = case["rho_a"].shape
+    rng = np.random.default_rng(3)
+    u = rng.uniform(-0.02, 0.02, (2,) + shape)
+    sims = [Simulation(case["params"], case["rho_a"], case["rho_b"], case["temp"], ux0=u[0], uy0=u[1],
+                       solid=case.get("solid"), t_bottom=case["t_bottom"], precision="fp64",
+                       launch={"fused": f}) for f in ("auto", "never")]
+
+    def compare():
+        got, ref = ((s.fields(), s.observables(), s.stress(), s.populations()) for s in sims)
+        errs = field_errors(got[0], ref[0])
+        assert max(errs.values()) <= 1e-13, errs
+        for k in ref[1]:
+            assert got[1][k] == pytest.approx(ref[1][k], rel=1e-12, abs=1e-14), k
+        for k in ref[2]:
+            assert rel(got[2][k], ref[2][k]) <= 1e-12, k
+        assert max(pop_errors(got[3], ref[3]).values()) <= 1e-13
+
+    compare()
+    for n in (0, 5, 0, 1):
+        for s in sims:
+            s.step(n)
+        for scale in (1.0, 1.3):
+            for s in sims:
+                s.set_bottom_temperature(scale * case["t_bottom"])
+            compare()
+    for s in sims:
+        s.step(3)
+    compare()
+
+
+@pytest.mark.parametrize("n,ckpt", [(1, 1), (2, 1), (30, 1), (1, 4), (8, 4), (9, 4), (30, 7)])
+def test_taped_moment_run_leaves_the_state_of_plain_steps(n, ckpt):
+    """The taped run's state, previous level (stress) and loss are those of
+    tlb_step, wherever checkpoints fall; its gradient is that of the
+    population run."""
+    case = workloads.small()
+    a, b, c = make(case, "fp64"), make(case, "fp64"), make(case, "fp64", "never")
+    for s in (a, b, c):
+        s.step(3)
+    loss, ref = a.forward_taped(n, ckpt), c.forward_taped(n, ckpt)
+    b.step(n)
+    assert np.array_equal(a.populations(), b.populations())
+    sa, sb = a.stress(), b.stress()
+    for k in sa:
+        assert np.array_equal(sa[k], sb[k]), k
+    assert loss == pytest.approx(ref, rel=1e-13)
+    g, r = a.adjoint(n), c.adjoint(n)
+    assert np.abs(g - r).max() <= 1e-11 * np.abs(r).max()
+    a.step(2)
+    b.step(2)
+    assert np.array_equal(a.populations(), b.populations())
+
+
+def test_moment_state_translates_bitwise():
+    """A start shifted by 37 columns gives the shifted result bit for bit: no
+    column depends on where its wavefront begins."""
+    case = posts_case(lx=150, ly=60, seed=9)
+    a = make(case, "fp32")
+    sh = lambda z: np.roll(z, 37, axis=-1)
+    b = make(dict(params=case["params"], **{k: sh(case[k]) for k in ("rho_a", "rho_b", "temp", "solid", "t_bottom")}),
+             "fp32")
+    a.step(60)
+    b.step(60)
+    fa, fb = a.fields(), b.fields()
+    for k in fa:
+        assert np.array_equal(sh(fa[k]), fb[k]), k
+
+
+@pytest.mark.parametrize("name", ["small", "posts", "three_strips_short", "narrow"])
+@pytest.mark.parametrize("lanes", [128, 256])
+def test_fp32_moment_steps_are_the_fused_launches_bit_for_bit(name, lanes):
+    """FP32 moment steps evaluate the fused launches' operations one by one:
+    populations and fields are the same bits after calls of any length, so a
+    trajectory does not depend on which of them took it."""
+    case = CASES[name]()
+    a = make(case, "fp32")
+    b = Simulation(case["params"], case["rho_a"], case["rho_b"], case["temp"], solid=case.get("solid"),
+                   t_bottom=case.get("t_bottom"), precision="fp32",
+                   launch={"fused": "always", "fused_lanes": lanes})
+    for n in (0, 1, 2, 3, 4, 9, 60):
+        a.step(n)
+        b.step(n)
+        assert np.array_equal(a.populations(), b.populations()), (n, a.t)
+        fa, fb = a.fields(), b.fields()
+        for k in fa:
+            assert np.array_equal(fa[k], fb[k]), (n, a.t, k)
