@@ -19,6 +19,7 @@
 #include "lb_kernels.hpp"
 #include "lb_moment.hpp"
 #include "lb_reduce.hpp"
+#include "readout.hpp"
 
 namespace {
 
@@ -68,6 +69,7 @@ struct tlb_handle {
   void* drop_acc = nullptr;        // per droplet: sums, root, output record
   size_t drop_acc_cap = 0;         // droplets drop_acc has room for
   double* export_buf = nullptr;    // [27][ly][lx], allocated on first use
+  tlbh::Readout readout;           // copies of results to the caller
   double n_fluid = 0, n_top = 0;
   std::vector<uint8_t> host_solid;  // [ly*lx] solid flags (host copy)
   std::vector<double> host_tb;      // [lx] bottom wall temperature (host copy)
@@ -678,12 +680,13 @@ int run_droplets(tlb_handle* h, const char* who, DropBuffers& b, bool grow, doub
     TLB_HIP(h, hipGetLastError());
   }
   const int64_t m = std::min<int64_t>(cap, total);
-  if (m > 0)
-    TLB_HIP(h, hipMemcpyAsync(out, a.out, (size_t)m * sizeof(tlb_droplet), hipMemcpyDeviceToHost,
-                              h->stream));
-  if (labels)
-    TLB_HIP(h, hipMemcpyAsync(labels, a.label, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost,
-                              h->stream));
+  auto fetch = [&](void* dst, const void* src, size_t bytes) {
+    // (a call that must not allocate keeps to the runtime's own copy)
+    return grow ? h->readout.fetch(src, bytes, 1, &dst, h->stream)
+                : hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, h->stream);
+  };
+  if (m > 0) TLB_HIP(h, fetch(out, a.out, (size_t)m * sizeof(tlb_droplet)));
+  if (labels) TLB_HIP(h, fetch(labels, a.label, (size_t)n * sizeof(int32_t)));
   TLB_HIP(h, hipStreamSynchronize(h->stream));
   return TLB_OK;
 }
@@ -1073,12 +1076,8 @@ int tlb_get_fields(tlb_handle* h, double* rho_a, double* rho_b, double* ux, doub
   if (!h->fields) TLB_HIP(h, hipMalloc(&h->fields, 7 * n * sizeof(double)));
   int rc = evaluate_time_level(h, Level::kFields);
   if (rc != TLB_OK) return rc;
-  double* outs[5] = {rho_a, rho_b, ux, uy, temp};
-  for (int k = 0; k < 5; ++k)
-    if (outs[k])
-      TLB_HIP(h, hipMemcpyAsync(outs[k], h->fields + k * n, n * sizeof(double),
-                                hipMemcpyDeviceToHost, h->stream));
-  TLB_HIP(h, hipStreamSynchronize(h->stream));
+  void* outs[5] = {rho_a, rho_b, ux, uy, temp};
+  TLB_HIP(h, h->readout.fetch(h->fields, n * sizeof(double), 5, outs, h->stream));
   return TLB_OK;
 }
 
@@ -1088,12 +1087,8 @@ int tlb_get_stress(tlb_handle* h, double* sxy_visc, double* pxy_int) {
   if (!h->fields) TLB_HIP(h, hipMalloc(&h->fields, 7 * n * sizeof(double)));
   int rc = evaluate_time_level(h, Level::kStress);
   if (rc != TLB_OK) return rc;
-  double* outs[2] = {sxy_visc, pxy_int};
-  for (int k = 0; k < 2; ++k)
-    if (outs[k])
-      TLB_HIP(h, hipMemcpyAsync(outs[k], h->fields + (5 + k) * n, n * sizeof(double),
-                                hipMemcpyDeviceToHost, h->stream));
-  TLB_HIP(h, hipStreamSynchronize(h->stream));
+  void* outs[2] = {sxy_visc, pxy_int};
+  TLB_HIP(h, h->readout.fetch(h->fields + 5 * n, n * sizeof(double), 2, outs, h->stream));
   return TLB_OK;
 }
 
@@ -1108,12 +1103,8 @@ int tlb_row_averages(tlb_handle* h, double* u_av, double* pxy_av) {
   hipLaunchKernelGGL(tlbk::lb_row_averages, dim3(ly), dim3(256), 0, h->stream, h->fields, h->solid,
                      lx, ly, h->rows, h->rows + ly);
   TLB_HIP(h, hipGetLastError());
-  double* outs[2] = {u_av, pxy_av};
-  for (int k = 0; k < 2; ++k)
-    if (outs[k])
-      TLB_HIP(h, hipMemcpyAsync(outs[k], h->rows + (size_t)k * ly, ly * sizeof(double),
-                                hipMemcpyDeviceToHost, h->stream));
-  TLB_HIP(h, hipStreamSynchronize(h->stream));
+  void* outs[2] = {u_av, pxy_av};
+  TLB_HIP(h, h->readout.fetch(h->rows, ly * sizeof(double), 2, outs, h->stream));
   return TLB_OK;
 }
 
@@ -1191,9 +1182,8 @@ int tlb_get_populations(tlb_handle* h, double* out) {
     });
   }
   TLB_HIP(h, hipGetLastError());
-  TLB_HIP(h, hipMemcpyAsync(out, h->export_buf, total * sizeof(double), hipMemcpyDeviceToHost,
-                            h->stream));
-  TLB_HIP(h, hipStreamSynchronize(h->stream));
+  void* outs[1] = {out};
+  TLB_HIP(h, h->readout.fetch(h->export_buf, total * sizeof(double), 1, outs, h->stream));
   return TLB_OK;
 }
 
