@@ -33,6 +33,11 @@ class Readout {
     if (ring_) (void)hipHostFree(ring_);
   }
 
+  // Page-locked memory of at least 64 KiB that a kernel may write, for results
+  // read after the stream is waited for and before the next use of this
+  // object; null when there is none.
+  void* page() { return reserve(kPage) == hipSuccess ? ring_ : nullptr; }
+
   // `parts` blocks of `bytes` bytes, one after the other in device memory, to
   // dst[0 .. parts - 1] (those that are not null), after the work on `stream`;
   // returns when they are there.
@@ -54,6 +59,7 @@ class Readout {
   // the link 73 us. Threads that fault in one huge page of a destination each
   // clear it, so a piece is what lies in one 2 MiB window of it.
   static constexpr size_t kChunk = (size_t)4 << 20, kWindow = (size_t)2 << 20;
+  static constexpr size_t kPage = (size_t)64 << 10;
   static constexpr size_t kOneCopy = (size_t)2 << 20, kThreaded = (size_t)16 << 20;
   static constexpr int kSlots = 4;
   static constexpr size_t kPerThread = (size_t)8 << 20;
@@ -68,10 +74,10 @@ class Readout {
   // at half the cost of a fault each (where the kernel cannot, by faults).
   static void place(const Piece& p, const char* ring) {
 #ifdef MADV_POPULATE_WRITE
-    constexpr uintptr_t kPage = 4096;
-    const uintptr_t a = (reinterpret_cast<uintptr_t>(p.dst) + kPage - 1) & ~(kPage - 1);
-    const uintptr_t b = (reinterpret_cast<uintptr_t>(p.dst) + p.len) & ~(kPage - 1);
-    if (b > a + 16 * kPage) (void)madvise(reinterpret_cast<void*>(a), b - a, MADV_POPULATE_WRITE);
+    constexpr uintptr_t kUnit = 4096;
+    const uintptr_t a = (reinterpret_cast<uintptr_t>(p.dst) + kUnit - 1) & ~(kUnit - 1);
+    const uintptr_t b = (reinterpret_cast<uintptr_t>(p.dst) + p.len) & ~(kUnit - 1);
+    if (b > a + 16 * kUnit) (void)madvise(reinterpret_cast<void*>(a), b - a, MADV_POPULATE_WRITE);
 #endif
     constexpr size_t kRing = kSlots * kChunk;
     const size_t at = p.off % kRing, m1 = std::min(p.len, kRing - at);
@@ -99,7 +105,7 @@ class Readout {
       return e;
     }
     const size_t n = (total + kChunk - 1) / kChunk;
-    e = reserve(total <= kOneCopy ? (total + 65535) & ~(size_t)65535 : kSlots * kChunk);
+    e = reserve(total <= kOneCopy ? std::max(total, kPage) : kSlots * kChunk);
     if (e != hipSuccess) return e;
     char* ring = static_cast<char*>(ring_);
     if (total <= kOneCopy) {

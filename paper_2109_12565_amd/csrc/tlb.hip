@@ -1051,11 +1051,14 @@ int tlb_observables(tlb_handle* h, tlb_obs* out) {
   oa.dt_nominal = h->p.dt_nominal;
   oa.ly = h->p.ly;
   oa.dtdy_sum = h->dtdy_sum;
-  oa.out = h->obs;
+  // the kernel writes its six values to the host's memory itself: a copy of
+  // them costs as much as the kernel (step and observables at 128 x 64: 37 us,
+  // 28 without)
+  const double* v = static_cast<const double*>(h->readout.page());
+  if (!v) return fail(h, TLB_ENOMEM, "tlb_observables: no page-locked memory");
+  oa.out = const_cast<double*>(v);
   hipLaunchKernelGGL(tlbk::lb_reduce_observables, dim3(1), dim3(256), 0, h->stream, oa);
   TLB_HIP(h, hipGetLastError());
-  double v[6];
-  TLB_HIP(h, hipMemcpyAsync(v, h->obs, sizeof v, hipMemcpyDeviceToHost, h->stream));
   TLB_HIP(h, hipStreamSynchronize(h->stream));
   out->step = h->t;
   out->mass_a = v[0];
