@@ -163,12 +163,23 @@ tlbh::Geometry choose_launch(const tlb_params& p, size_t buffer_bytes, bool soli
   const int target = std::max(1, std::min(per_cu, target_waves / (l.bx / 64)));
   const long long strips = (lx + l.bx - 1) / l.bx;
   long long rows = (ly * strips + (long long)cus * target - 1) / ((long long)cus * target);
-  // Floor of 5 rows: each chunk pulls 4 extra rows, and lattices too small
-  // to give every CU its target waves (1024 x 512: 2 rows) trade occupancy
-  // against that overhead best there (measured 36.6 us per step at 5 rows,
-  // 39.0 at 2, 41.0 at 8, 48.0 at 11).
+  // Floor of 5 rows: each chunk pulls 4 extra rows, and lattices that give a CU
+  // fewer than its target waves trade occupancy against that overhead best
+  // there (1024 x 512 FP32: 36.6 us per step at 5 rows, 39.0 at 2, 41.0 at 8,
+  // 48.0 at 11). On smaller ones a chunk's chain of rows is the whole time:
+  // chunks of 2 rows while they are at most 13 waves per CU in FP32 and 6 in
+  // FP64, of 1 while at most 4 (FP32, 5 / 2 / 1 rows: 768 x 400 28.3 / 25.8 /
+  // 33.8 us, 512 x 256 23.4 / 15.5 / 16.5, 128 x 64 20.7 / 12.1 / 10.6; FP64:
+  // 768 x 400 39.0 / 49.8 / 61.2, 512 x 256 29.6 / 22.1 / 26.5, 128 x 64 25.3 /
+  // 15.1 / 13.4).
   rows = rows < 5 ? 5 : (rows > 65 ? 65 : rows);
   while ((rows + 4) % 3) ++rows;
+  if (storage_bytes(p.precision) >= 4) {
+    const long long few = p.precision == TLB_FP64 ? 6 : 13;
+    auto waves = [&](long long r) { return (ly + r - 1) / r * strips * (l.bx / 64); };
+    if (waves(1) <= 4LL * cus) rows = 1;
+    else if (waves(2) <= few * cus) rows = 2;
+  }
   if (p.rows > 0) rows = p.rows;
   l.rows = (int)(rows < ly ? rows : ly);
   l.grid = dim3((unsigned)strips, (unsigned)((ly + l.rows - 1) / l.rows), 1);
