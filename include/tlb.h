@@ -79,8 +79,8 @@ enum tlb_launch_flags {
 
 /* tlb_params.fused: use of the fused two-step kernel (see tlb_step). */
 enum tlb_fused_mode {
-  TLB_FUSED_AUTO = 0,    /* the library's choice: moment steps in FP64 and FP32
-                            (see tlb_step), else fused where it pays */
+  TLB_FUSED_AUTO = 0,    /* the library's choice: moment steps in FP64, FP32
+                            and FP16 (see tlb_step), else fused where it pays */
   TLB_FUSED_NEVER = 1,   /* single population steps */
   TLB_FUSED_ALWAYS = 2   /* wherever it applies */
 };
@@ -191,10 +191,12 @@ int tlb_init_external(tlb_handle **out, const tlb_params *p, const double *rho_a
  * streaming with bounce-back / anti-bounce-back at solid links, moments,
  * forces, velocity shift (Eq. (6)) and BGK collision. Enqueues only. With
  * tau = tau_g = 1 (the collision then returns the equilibria of Eqs. (3),
- * (18)), FP64 and FP32 handles below 4 GiB of populations keep, with fused =
- * TLB_FUSED_AUTO and no other fused option, the five moments rho_A, rho_B, j
- * and T per node in place of the populations and advance those, one launch
- * a step; the populations are formed where a call asks for them. Otherwise
+ * (18)), FP64, FP32 and FP16_DEV handles below 4 GiB of populations keep,
+ * with fused = TLB_FUSED_AUTO and no other fused option, the five moments
+ * rho_A, rho_B, j and T per node in place of the populations and advance
+ * those, one launch a step; the populations are formed where a call asks for
+ * them (FP16_DEV: the moments are FP32 sums of populations rounded to 16 bits
+ * as stored ones would be). Otherwise
  * pairs of steps may run as one fused launch where the handle's storage and
  * lattice allow it (see tlb_launch_info; flat walls at rest or moving, posts
  * allowed); the last step of a call is then a single step, which also forms
@@ -327,8 +329,8 @@ int64_t tlb_time(const tlb_handle *h);
  * the fused two-step kernel applies (tau = tau_g = 1, flat walls at rest or
  * moving; blocks of fused_lanes lanes, strips of fused_strip stored columns,
  * chunks of fused_rows rows): tlb_step advances pairs of steps with it, ending
- * each call with a single step, unless the handle advances moments (FP64 and
- * FP32 with TLB_FUSED_AUTO, see tlb_step). Host struct, written by the
+ * each call with a single step, unless the handle advances moments (with
+ * TLB_FUSED_AUTO, see tlb_step). Host struct, written by the
  * call. Returns TLB_EINVAL on a NULL argument. */
 typedef struct tlb_launch {
   int32_t bx, rows, grid_x, grid_y;

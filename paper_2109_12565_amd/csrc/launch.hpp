@@ -56,6 +56,7 @@ struct Device {
   // FP32 moment step that a fused launch takes in a pair (see
   // tlbk::kSameRounding): its first or its second step
   bool pair_first = false, pair_second = false;
+  bool src_full = false;  // 16-bit storages: the step before was a pair's second
 };
 
 // Kernel passes of the step kernel.

@@ -162,10 +162,12 @@ void launch_step2(const Device& d, const void* src, void* dst, Pass pass, void* 
   }
 }
 
-// Storages with the moment state: those whose populations are stored in the
-// compute type (the 16-bit ones round every stored population).
+// Storages with the moment state. Not the fixed-point one, whose 27 planes have
+// no room for three sets of FP32 moments, and not BF16, whose population
+// kernels are compiled to roundings that equilibria_stored does not repeat at
+// every node (a flip of 2^-8 of a deviation now and then).
 template <class St>
-constexpr bool kHasMoments = !St::kFix && !St::kDev;
+constexpr bool kHasMoments = !St::kFix && !std::is_same_v<St, tlbk::StoreBF16Dev>;
 
 template <class St, unsigned kMode>
 void launch_moment_kernel(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
@@ -215,9 +217,10 @@ void launch_moment(const Device& d, MomentPass pass, const void* src, void* dst)
   a.tiles = static_cast<const MomentTile*>(d.tiles);
   a.ntiles = d.ntiles;
   a.nlinked = d.nlinked;
+  a.src_full = d.src_full;
   // (the fused kernel without solid cells loads T_w, and with it 2 w T_w, in a
-  // block of its own at both levels, the one with solid cells at its second)
-  a.round_wall = d.pair_second || (d.pair_first && !d.has_solid);
+  // block of its own at both levels, the others at the second)
+  a.round_wall = d.pair_second || (d.pair_first && !d.has_solid && !St::kDev);
   a.out = static_cast<double*>(dst);
   const tlb_params& p = *d.p;
   // combined from the constants as the population kernels round them, so
@@ -236,7 +239,9 @@ void launch_moment(const Device& d, MomentPass pass, const void* src, void* dst)
   a.x2 = C((double)a.s.g12 * w(2) * (double)a.s.inv_rho0 * (double)a.s.inv_rho0);
   switch (pass) {
     case MomentPass::kStep: launch_moment_step<St>(d, a); break;
-    case MomentPass::kStepTopRow: launch_moment_split<St, kMomStep | kModeTopRow>(d, a); break;
+    case MomentPass::kStepTopRow:  // the adjoint's
+      if constexpr (kHasAdjoint<St>) launch_moment_split<St, kMomStep | kModeTopRow>(d, a);
+      break;
     case MomentPass::kObserve: launch_moment_solid<St, kMomObserve>(d, a); break;
     case MomentPass::kFields: launch_moment_solid<St, kMomFields>(d, a); break;
     case MomentPass::kExport: launch_moment_solid<St, kMomExport>(d, a); break;
@@ -348,7 +353,8 @@ void Launcher<St>::init_moments(const Device& d, void* dst, const double* rho_a,
     dim3 grid((p.lx + 255) / 256, p.ly, 1);
     hipLaunchKernelGGL(tlbk::lb_moment_init<St>, grid, dim3(256), 0, d.stream,
                        static_cast<C*>(dst), rho_a, rho_b, temp, ux0, uy0, d.solid, p.lx, d.pitch,
-                       d.pop_stride, C(p.rho_wall[0]), C(p.rho_wall[1]));
+                       d.pop_stride, C(p.rho_wall[0]), C(p.rho_wall[1]), C(p.rho_ref[0]),
+                       C(p.rho_ref[1]), C(p.t_ref));
   }
 }
 

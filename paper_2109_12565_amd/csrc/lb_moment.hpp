@@ -1,5 +1,5 @@
 // Time step of the moment state for tau = tau_g = 1 (arXiv:2109.12565, Sec. 2),
-// FP64 and FP32, solid cells allowed, flat walls at rest or moving along x.
+// FP64, FP32 and 16-bit FP16 storage, solid cells allowed, flat walls at rest or moving along x.
 //
 // At tau = tau_g = 1 the BGK collision (Eqs. (2), (16)) returns the
 // equilibria (Eqs. (3), (18)), so the post-collision populations of time t
@@ -35,7 +35,8 @@
 // kSameRounding) takes 97. FP64 178 us, 671 MB = 3.8 TB/s. Before: 263 and 677
 // us a step (two-step kernel), 377 and 752 (single steps). Smaller lattices:
 // FP32 15.7 us at 1024 x 512 (25.3), 6.1 at 128 x 64 (12); FP64 17.8 (52.2) and
-// 6.4 (17).
+// 6.4 (17). FP16 storage 130 us at 4096 x 2048 (247 in the two-step kernel), the
+// rounding adding a tenth to the FP32 instructions.
 #pragma once
 
 #include <utility>
@@ -76,6 +77,7 @@ struct MomentArgs {
   int strip;      // stored columns per wavefront (at most kMomStrip)
   const MomentTile* tiles;  // steps with solid cells: the wavefronts' tiles,
   int ntiles, nlinked;      // the nlinked first ones hold solid links
+  bool src_full;    // deviation storages: src holds full values (see equilibria_stored)
   bool round_wall;  // kSameRounding: 2 w T_w rounded before a population is taken off
   // stencil weights ga w(|c|^2) + gr p(|c|^2) of the self forces, per
   // component, for offsets of 1 (g) and times the offset 2 (h); g12 w(2) /
@@ -113,6 +115,13 @@ __device__ inline double recip_newton(double v) {
   double r = __builtin_amdgcn_rcp(v);
   r = fma(r, fma(-v, r, 1.0), r);
   return fma(r, fma(-v, r, 1.0), r);
+}
+
+// As the storage's population kernels have it (16-bit: the hardware's).
+template <class St>
+__device__ inline typename St::C recip_moment(typename St::C v) {
+  if constexpr (St::kFast) return recip<St>(v);
+  else return recip_newton(v);
 }
 
 // psi_s = rho0 (1 - e^x), x = -rho / rho0 (Eq. (12)), as -rho0 (2^k (e^f - 1) +
@@ -182,6 +191,39 @@ __device__ inline void equilibria(double rho, double tx, double ty, double (&f)[
 // events. FP64 has no such need at 1e-13 and takes the shorter forms above.
 template <typename C> constexpr bool kSameRounding = sizeof(C) == 4;
 
+// The FP16 deviation storage keeps its moments in FP32: what its populations, rounded to 16 bits where a launch of the population kernels
+// would have stored them, add up to. They are rounded in registers, after
+// every step but the first of a pair (kMomSplit: the second one's start), so a
+// run gives the results of 16-bit populations while 40 bytes a node move
+// instead of 120. Moments of rounded populations are deviations from the
+// references (rho - rho_ref, T - t_ref, exact sums), those of the others full
+// values, as the fused kernel has them.
+
+// The nine populations of a 16-bit storage as it stores them, in stored form:
+// deviations w rho q - w ref +- D rounded to 16 bits, the rest population the
+// remainder of `dev`, the node's deviation.
+template <class St>
+__device__ inline void equilibria_stored(float rho, float dev, float ref, float ux, float uy,
+                                         float (&f)[9]) {
+#pragma clang fp contract(off)
+  const float u2 = fma(ux, ux, uy * uy);
+  float sum = 0;
+  auto pair = [&](auto ic, float cu) {
+    constexpr int I = decltype(ic)::value, J = Dir<I>::opp;
+    constexpr float w = w_dir<float>(I);
+    const float wr = w * rho, q = fma(-1.5f, u2, fma(cu, 4.5f * cu, 1.0f));
+    const float even = fma(wr, q, -(w * ref)), d = (3.0f * w) * rho;
+    f[I] = St::stored(fma(d, cu, even));
+    f[J] = St::stored(fma(-d, cu, even));
+    sum = I == 1 ? f[I] + f[J] : sum + (f[I] + f[J]);
+  };
+  pair(std::integral_constant<int, 1>{}, ux);
+  pair(std::integral_constant<int, 2>{}, uy);
+  pair(std::integral_constant<int, 5>{}, ux + uy);
+  pair(std::integral_constant<int, 6>{}, uy - ux);
+  f[0] = dev - sum;
+}
+
 // The nine equilibria in the population kernels' operations: opposite ones
 // w rho q +- D with one rounding each, the rest population the remainder of
 // their sum. kSplit: as the fused kernel's second level pulls them from the
@@ -248,6 +290,18 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   // offsets, the column the lane's
   const uint32_t row_b = (uint32_t)a.pitch * sizeof(C);
   const uint32_t plane_b = (uint32_t)a.pop_stride * sizeof(C);
+  // 16-bit storages: what a loaded density or temperature misses to the full
+  // value, and to the deviation
+  constexpr bool kDev = St::kDev;
+  [[maybe_unused]] const C ref[3] = {a.ref_a, a.ref_b, a.ref_t};
+  [[maybe_unused]] C to_full[3] = {0, 0, 0}, to_dev[3] = {0, 0, 0};
+  if constexpr (kDev) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      to_full[k] = ma.src_full ? C(0) : ref[k];
+      to_dev[k] = ma.src_full ? -ref[k] : C(0);
+    }
+  }
   const PopMem<Store<C>, 0> msrc(a.src, (uint64_t)plane_b * 5);
   const uint32_t vcol = (uint32_t)xw * sizeof(C);
   // Lanes that store nothing get an offset beyond the five planes (which are
@@ -260,6 +314,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   // five rows in use and kAhead rows of loads in flight.
   constexpr int R = kMomRing<C>, kAhead = R - 3;
   C rho[R][2], mx[R], my[R], tt[R];   // loaded moments
+  [[maybe_unused]] C raw[R][2];       // kDev: densities as loaded
   C psi[R][2], dpx[R][2], drx[R][2];  // psi and the x-differences of psi and rho
   constexpr bool kSame = kSameRounding<C>, kSplit = (kMode & kMomSplit) != 0;
   [[maybe_unused]] C dp2[R][2];       // kSame: psi(x + 2) - psi(x - 2)
@@ -286,14 +341,14 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
     constexpr int S = decltype(slot)::value;
     if (decltype(inside)::value || (r >= 0 && r < ly)) {
       const uint32_t s = (uint32_t)r * row_b;
-      rho[S][0] = msrc.ld(s, vcol);
-      rho[S][1] = msrc.ld(s + plane_b, vcol);
+      (kDev ? raw : rho)[S][0] = msrc.ld(s, vcol);
+      (kDev ? raw : rho)[S][1] = msrc.ld(s + plane_b, vcol);
       mx[S] = msrc.ld(s + 2 * plane_b, vcol);
       my[S] = msrc.ld(s + 3 * plane_b, vcol);
       tt[S] = msrc.ld(s + 4 * plane_b, vcol);
     } else {
-      rho[S][0] = a.rho_wall0;
-      rho[S][1] = a.rho_wall1;
+      (kDev ? raw : rho)[S][0] = a.rho_wall0 - to_full[0];
+      (kDev ? raw : rho)[S][1] = a.rho_wall1 - to_full[1];
     }
   };
 
@@ -305,8 +360,9 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
     const bool solid = kSolid && (lm_d & kSelfSolid) != 0;
     const uint32_t o = (uint32_t)d * row_b;
     // solid nodes hold the wetting densities and nothing else
-    mdst.put(o, vout, solid ? a.rho_wall0 : n[0]);
-    mdst.put(o + plane_b, vout, solid ? a.rho_wall1 : n[1]);
+    const C off0 = kDev && !kSplit ? ref[0] : C(0), off1 = kDev && !kSplit ? ref[1] : C(0);
+    mdst.put(o, vout, solid ? a.rho_wall0 - off0 : n[0]);
+    mdst.put(o + plane_b, vout, solid ? a.rho_wall1 - off1 : n[1]);
     mdst.put(o + 2 * plane_b, vout, solid ? C(0) : jx);
     mdst.put(o + 3 * plane_b, vout, solid ? C(0) : jy);
     mdst.put(o + 4 * plane_b, vout, solid ? C(0) : n[2]);
@@ -328,8 +384,9 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
     C v1n[2];
 #pragma unroll
     for (int l = 0; l < 2; ++l) {
+      if constexpr (kDev) rho[S][l] = raw[S][l] + to_full[l];
       if constexpr (kSame) {
-        psi[S][l] = psi_exp(rho[S][l], a.rho0, a.inv_rho0);
+        psi[S][l] = psi_of<St>(rho[S][l], a.rho0, a.inv_rho0);
         const C left = from_left(psi[S][l]), right = from_right(psi[S][l]);
         dpx[S][l] = right - left;
         dp2[S][l] = from_right(right) - from_left(left);
@@ -347,7 +404,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
       return;
     }
     uint32_t lq = 0;
-    const C ra = rho[Q][0], rb = rho[Q][1], temp = tt[Q];
+    const C ra = rho[Q][0], rb = rho[Q][1], temp = kDev ? tt[Q] + to_full[2] : tt[Q];
     C vx[3], vy[3];  // velocities (scaled unless kSame) of the three equilibria at row q
     {
       if constexpr (!kIn) lq = link_mask<kFlags>(a, xw, q);
@@ -407,7 +464,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
         }
       }
       // ---- velocities (u and u^H of the observables; scaled ones below)
-      const C inv_rho = recip_newton(ra + rb);
+      const C inv_rho = recip_moment<St>(ra + rb);
       const C Fx = FA[0] + FB[0], Fy = FA[1] + FB[1];
       if constexpr ((kMode & (kMomObserve | kMomFields)) != 0) {
         if (out_lane && q < y1) {
@@ -423,26 +480,30 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
             hx = fma(C(0.5), Fx, mx[Q]) * inv_rho;
             hy = fma(C(0.5), Fy, my[Q]) * inv_rho;
           }
+          // (deviations: the reference added in double)
+          const double da = kDev ? (double)ref[0] + (double)(raw[Q][0] + to_dev[0]) : (double)ra;
+          const double db = kDev ? (double)ref[1] + (double)(raw[Q][1] + to_dev[1]) : (double)rb;
+          const double dt = kDev ? (double)ref[2] + (double)(tt[Q] + to_dev[2]) : (double)temp;
           if constexpr ((kMode & kMomObserve) != 0) {
             if (!solid) {
-              acc[0] += (double)ra;
-              acc[1] += (double)rb;
-              acc[2] += (double)temp;
-              acc[3] += (double)hy * (double)temp;
+              acc[0] += da;
+              acc[1] += db;
+              acc[2] += dt;
+              acc[3] += (double)hy * dt;
               acc[4] += (double)hx * (double)hx + (double)hy * (double)hy;
-              if (q == ly - 1) acc[5] += (double)temp - (double)a.t_top;
+              if (q == ly - 1) acc[5] += dt - (double)a.t_top;
             }
           } else {
             const size_t nn = (size_t)lx * ly, o = (size_t)q * lx + xl;
-            C tv = temp;
+            double tv = dt;
             if constexpr (kSolid) {
-              if (solid) tv = solid_temperature(a, xl, q);
+              if (solid) tv = (double)solid_temperature(a, xl, q);
             }
-            a.fields[o] = (double)ra;
-            a.fields[nn + o] = (double)rb;
+            a.fields[o] = solid ? (double)a.rho_wall0 : da;
+            a.fields[nn + o] = solid ? (double)a.rho_wall1 : db;
             a.fields[2 * nn + o] = solid ? 0.0 : (double)hx;
             a.fields[3 * nn + o] = solid ? 0.0 : (double)hy;
-            a.fields[4 * nn + o] = (double)tv;
+            a.fields[4 * nn + o] = tv;
           }
         }
         v1[0] = v1n[0];
@@ -456,7 +517,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
         for (int i = 0; i < 3; ++i) vx[i] = ux, vy[i] = uy;
       } else {
         const C scale = kSame ? C(1) : C(kVelScale);
-        const C tA = recip_newton(ra) * scale, tB = recip_newton(rb) * scale;
+        const C tA = recip_moment<St>(ra) * scale, tB = recip_moment<St>(rb) * scale;
         vx[0] = fma(FA[0], tA, ux), vy[0] = fma(FA[1], tA, uy);
         vx[1] = fma(FB[0], tB, ux), vy[1] = fma(FB[1], tB, uy);
         vx[2] = fma(C(0.5) * Fx, k, ux), vy[2] = fma(C(0.5) * Fy, k, uy);
@@ -465,19 +526,34 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
     v1[0] = v1n[0];
     v1[1] = v1n[1];
     const C dens[3] = {ra, rb, temp};
+    [[maybe_unused]] C dev[3] = {0, 0, 0};  // deviation storages
+    if constexpr (kDev)
+      dev[0] = raw[Q][0] + to_dev[0], dev[1] = raw[Q][1] + to_dev[1], dev[2] = tt[Q] + to_dev[2];
     if constexpr ((kMode & (kMomExport | kMomPost)) != 0) {
       if (!out_lane || q >= y1) return;
       const bool solid = kSolid && !kIn && (lq & kSelfSolid) != 0;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         C f[9];
-        if constexpr (kSame) equilibria_same<false>(dens[k], vx[k], vy[k], f);
+        if constexpr (kDev) equilibria_stored<St>(dens[k], dev[k], ref[k], vx[k], vy[k], f);
+        else if constexpr (kSame) equilibria_same<false>(dens[k], vx[k], vy[k], f);
         else equilibria(dens[k], vx[k], vy[k], f);
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
-          if constexpr ((kMode & kMomExport) != 0)
-            ma.out[((size_t)(9 * k + i) * ly + q) * lx + xl] = solid ? 0.0 : (double)f[i];
-          else
+          if constexpr ((kMode & kMomExport) != 0) {
+            const double v = kDev ? fma(w_dir<double>(i), (double)ref[k], (double)f[i]) : (double)f[i];
+            ma.out[((size_t)(9 * k + i) * ly + q) * lx + xl] = solid ? 0.0 : v;
+          } else if constexpr (kDev) {  // in the storage's layout, rest planes last
+            using T = typename St::T;
+            static_assert(St::kRest32, "FP32 rest planes");
+            T* to = static_cast<T*>(a.dst);
+            const size_t o = (size_t)q * a.pitch + xl;
+            if (i == 0)
+              (reinterpret_cast<float*>(to + (size_t)27 * a.pop_stride) + (size_t)k * a.pop_stride)[o] =
+                  solid ? 0.0f : f[i];
+            else
+              to[(size_t)(9 * k + i) * a.pop_stride + o] = St::encode(solid ? C(0) : f[i]);
+          } else
             static_cast<C*>(a.dst)[(size_t)(9 * k + i) * a.pop_stride + (size_t)q * a.pitch + xl] =
                 solid ? C(0) : f[i];
         }
@@ -498,7 +574,8 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
         constexpr int k = decltype(kc)::value;
         constexpr bool kG = k == 2;
         C f[9];
-        equilibria_same<kSplit>(dens[k], vx[k], vy[k], f);
+        if constexpr (kDev && !kSplit) equilibria_stored<St>(dens[k], dev[k], ref[k], vx[k], vy[k], f);
+        else equilibria_same<kSplit>(dens[k], vx[k], vy[k], f);
         // the value v of direction I, bounced where the link of row `row` is
         // solid: `own` is the node's population of the opposite direction
         auto bounce = [&](auto ic, C& v, C own, uint32_t links, int row) {
@@ -507,7 +584,9 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
           v = own;
           if constexpr (kG) {
             constexpr C w2 = C(2) * w_dir<C>(I);
-            const C tw = source_wall_temperature<I, kFlags>(a, xw, row) * wall_even_factor<I, kFlags>(a, row);
+            const C ts = source_wall_temperature<I, kFlags>(a, xw, row);
+            const C even = wall_even_factor<I, kFlags>(a, row);
+            const C tw = kDev && !kSplit ? fma(ts, even, -ref[2]) : ts * even;
             v = ma.round_wall ? w2 * tw - own : fma(w2, tw, -own);
           }
         };
@@ -644,7 +723,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   for (int s = 0; s < R; ++s) {
     mx[s] = my[s] = tt[s] = C(0);
 #pragma unroll
-    for (int l = 0; l < 2; ++l) rho[s][l] = psi[s][l] = dpx[s][l] = dp2[s][l] = drx[s][l] = C(0);
+    for (int l = 0; l < 2; ++l) raw[s][l] = rho[s][l] = psi[s][l] = dpx[s][l] = dp2[s][l] = drx[s][l] = C(0);
   }
   unroll<kAhead>([&](auto k) { load_row(k, std::false_type{}, first + decltype(k)::value); });
   unroll<4>([&](auto k) { stage(k, Psi{}, first + decltype(k)::value); });
@@ -676,8 +755,9 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
           C d4 = up[k][0], d7 = from_right(up[k][1]), d8 = from_left(up[k][2]);
           if (k == 2) {
             constexpr C wa = C(2) * w_dir<C>(4), wd = C(2) * w_dir<C>(7);
-            const C t4 = a.t_top * wall_even_factor<4, kFlags>(a, ly - 1);
-            const C t7 = a.t_top * wall_even_factor<7, kFlags>(a, ly - 1);
+            const C e4 = wall_even_factor<4, kFlags>(a, ly - 1), e7 = wall_even_factor<7, kFlags>(a, ly - 1);
+            const C t4 = kDev && !kSplit ? fma(a.t_top, e4, -ref[2]) : a.t_top * e4;
+            const C t7 = kDev && !kSplit ? fma(a.t_top, e7, -ref[2]) : a.t_top * e7;
             d4 = ma.round_wall ? wa * t4 - d4 : fma(wa, t4, -d4);
             d7 = ma.round_wall ? wd * t7 - d7 : fma(wd, t7, -d7);
             d8 = ma.round_wall ? wd * t7 - d8 : fma(wd, t7, -d8);
@@ -772,7 +852,8 @@ __global__ __launch_bounds__(256) void lb_moment_init(
     const double* __restrict__ rho_b, const double* __restrict__ temp,
     const double* __restrict__ ux0, const double* __restrict__ uy0,
     const uint8_t* __restrict__ solid, int lx, int pitch, long long pop_stride,
-    typename St::C rho_wall0, typename St::C rho_wall1) {
+    typename St::C rho_wall0, typename St::C rho_wall1, typename St::C ref_a,
+    typename St::C ref_b, typename St::C ref_t) {
 #pragma clang fp contract(off)
   using C = typename St::C;
   const int x = blockIdx.x * 256 + threadIdx.x;
@@ -780,9 +861,10 @@ __global__ __launch_bounds__(256) void lb_moment_init(
   if (x >= lx) return;
   const size_t q = (size_t)y * lx + x, ps = (size_t)pop_stride;
   C* m = dst + (size_t)y * pitch + x;
+  const C ref[3] = {St::kDev ? ref_a : C(0), St::kDev ? ref_b : C(0), St::kDev ? ref_t : C(0)};
   if (solid[q] != 0) {
-    m[0] = rho_wall0;
-    m[ps] = rho_wall1;
+    m[0] = rho_wall0 - ref[0];
+    m[ps] = rho_wall1 - ref[1];
     m[2 * ps] = m[3 * ps] = m[4 * ps] = C(0);
     return;
   }
@@ -796,12 +878,17 @@ __global__ __launch_bounds__(256) void lb_moment_init(
     const C shape = w_dir<C>(i) * fma(C(-1.5), u2, fma(cu, C(4.5) * cu, fma(cu, C(3), C(1))));
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      f[k][i] = dens[k] * shape;
-      sum[k] = fma(shape, dens[k], sum[k]);
+      if constexpr (St::kDev) {
+        f[k][i] = St::stored(fma(dens[k], shape, -(w_dir<C>(i) * ref[k])));
+        sum[k] += f[k][i];
+      } else {
+        f[k][i] = dens[k] * shape;
+        sum[k] = fma(shape, dens[k], sum[k]);
+      }
     }
   }
 #pragma unroll
-  for (int k = 0; k < 3; ++k) f[k][0] = dens[k] - sum[k];
+  for (int k = 0; k < 3; ++k) f[k][0] = (dens[k] - ref[k]) - sum[k];
   m[0] = sum9(f[0]);
   m[ps] = sum9(f[1]);
   m[2 * ps] = momentum_x(f[0], f[1]);

@@ -247,14 +247,15 @@ tlbh::Geometry choose_launch(const tlb_params& p, size_t buffer_bytes, bool soli
     }
   }
 
-  // Moment state: the library's own choice at tau = tau_g = 1 in FP64 and
-  // FP32 below 4 GiB (per step, moments / the launches it replaces, 4096 x
-  // 2048: FP32 127 / 263 us, FP64 178 / 677; 1024 x 512: 15.7 / 25.3, 17.8 /
-  // 52.2; 128 x 64: 6.1 / 12.0, 6.4 / 17.0). Any explicit choice of the fused
-  // kernel keeps that one.
+  // Moment state: the library's own choice at tau = tau_g = 1 in FP64, FP32 and
+  // FP16 storage below 4 GiB (per step, moments / the launches it replaces:
+  // FP32 4096 x 2048 127 / 263 us, 1024 x 512 15.7 / 25.3, 128 x 64 6.1 / 12.0;
+  // FP64 178 / 677, 17.8 / 52.2, 6.4 / 17.0; FP16 4096 x 2048 130 / 247). Any
+  // explicit choice of the fused kernel keeps that one.
   const bool moments = tau_one && !l.wide && p.fused == TLB_FUSED_AUTO && p.fused_rows == 0 &&
                        p.fused_strip == 0 && p.fused_lanes == 0 &&
-                       (p.precision == TLB_FP64 || p.precision == TLB_FP32);
+                       (p.precision == TLB_FP64 || p.precision == TLB_FP32 ||
+                        p.precision == TLB_FP16_DEV);
   if (moments) {
     // A chunk costs its rows and about three more (two of equilibria, four of
     // psi), so few tall chunks are best as long as every SIMD has its share:
@@ -386,6 +387,7 @@ void* moment_slot(const tlb_handle* h, int k) {
 void set_pair(tlbh::Device* d, int64_t s, int64_t n) {
   d->pair_first = s % 2 == 0 && s + 2 < n;
   d->pair_second = s % 2 == 1 && s + 1 < n;
+  d->src_full = s > 0 && s % 2 == 0;  // (the last steps of a run: s - 1 was a pair's second)
 }
 
 void launch_moment(const tlb_handle* h, tlbh::MomentPass pass, const void* src, void* dst,

@@ -1,4 +1,4 @@
-"""The moment state (tau = tau_g = 1, FP64 / FP32, the library's own choice)
+"""The moment state (tau = tau_g = 1, FP64, FP32 and FP16 storage, the library's own choice)
 against runs of population steps (fused = "never") and against the oracle.
 
 Both advance the same scheme; they differ in the order of sums and in the
@@ -148,16 +148,18 @@ def test_moment_state_translates_bitwise():
         assert np.array_equal(sh(fa[k]), fb[k]), k
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp16dev"])
 @pytest.mark.parametrize("name", ["small", "posts", "three_strips_short", "narrow"])
 @pytest.mark.parametrize("lanes", [128, 256])
-def test_fp32_moment_steps_are_the_fused_launches_bit_for_bit(name, lanes):
-    """FP32 moment steps evaluate the fused launches' operations one by one:
-    populations and fields are the same bits after calls of any length, so a
-    trajectory does not depend on which of them took it."""
+def test_moment_steps_are_the_fused_launches_bit_for_bit(precision, name, lanes):
+    """In FP32 arithmetic moment steps evaluate the fused launches' operations one
+    by one, the 16-bit rounding of stored populations included: populations and
+    fields are the same bits after calls of any length, so a trajectory does not
+    depend on which of them took it."""
     case = CASES[name]()
-    a = make(case, "fp32")
+    a = make(case, precision)
     b = Simulation(case["params"], case["rho_a"], case["rho_b"], case["temp"], solid=case.get("solid"),
-                   t_bottom=case.get("t_bottom"), precision="fp32",
+                   t_bottom=case.get("t_bottom"), precision=precision,
                    launch={"fused": "always", "fused_lanes": lanes})
     for n in (0, 1, 2, 3, 4, 9, 60):
         a.step(n)
