@@ -3,12 +3,14 @@
 //
 // A copy to ordinary memory is staged by the runtime, one thread filling the
 // destination, whose fresh pages are mapped and cleared on the way: 4096 x 2048
-// fields (336 MB) take 34 ms of it, where the link needs 6. From 16 MiB on the
-// copy engine fills a ring of page-locked chunks and several threads empty it
-// (9 to 12 ms). Up to 2 MiB all blocks come in one copy: 128 x 64 fields, with
-// the fields pass, 50 us (210 in five). Between the two neither is faster by
-// more than the runs differ, and the runtime's copy stays (12 MiB: 0.37 ms, the
-// ring 0.41).
+// fields (336 MB) take 34 ms of it, where the link needs 6. From 48 MiB in all,
+// or 32 MiB a block (which an allocator maps afresh each time), the copy
+// engine fills a ring of page-locked chunks and several threads empty it: 9 to
+// 12 ms; 32 MiB of droplet labels 1 ms (2). Up to 2 MiB all blocks come in one
+// copy: 128 x 64 fields, with the fields pass, 50 us (210 in five). Between
+// the two, where blocks are often recycled pages, the threads only compete
+// with the program's own: a run with its snapshot, ring / runtime, 17 MiB 2.7 /
+// 1.9 ms, 33 MiB 4.0 / 3.4, 49 MiB 4.0 / 4.7; without threads 2 to 4% slower.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -60,7 +62,7 @@ class Readout {
   // clear it, so a piece is what lies in one 2 MiB window of it.
   static constexpr size_t kChunk = (size_t)4 << 20, kWindow = (size_t)2 << 20;
   static constexpr size_t kPage = (size_t)64 << 10;
-  static constexpr size_t kOneCopy = (size_t)2 << 20, kThreaded = (size_t)16 << 20;
+  static constexpr size_t kOneCopy = (size_t)2 << 20, kThreaded = (size_t)48 << 20, kFresh = (size_t)32 << 20;
   static constexpr int kSlots = 4;
   static constexpr size_t kPerThread = (size_t)8 << 20;
   static constexpr int kMaxThreads = 8;
@@ -79,8 +81,7 @@ class Readout {
     const uintptr_t b = (reinterpret_cast<uintptr_t>(p.dst) + p.len) & ~(kUnit - 1);
     if (b > a + 16 * kUnit) (void)madvise(reinterpret_cast<void*>(a), b - a, MADV_POPULATE_WRITE);
 #endif
-    constexpr size_t kRing = kSlots * kChunk;
-    const size_t at = p.off % kRing, m1 = std::min(p.len, kRing - at);
+    const size_t at = p.off % (kSlots * kChunk), m1 = std::min(p.len, kSlots * kChunk - at);
     std::memcpy(p.dst, ring + at, m1);
     std::memcpy(p.dst + m1, ring, p.len - m1);
   }
@@ -99,7 +100,7 @@ class Readout {
     const size_t total = bytes * parts;
     if (total == 0) return hipSuccess;
     hipError_t e = hipSuccess;
-    if (total > kOneCopy && total < kThreaded) {
+    if (total > kOneCopy && total < kThreaded && bytes < kFresh) {
       for (int k = 0; k < parts && e == hipSuccess; ++k)
         e = hipMemcpyAsync(dst[k], src + k * bytes, bytes, hipMemcpyDeviceToHost, stream);
       return e;

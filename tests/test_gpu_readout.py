@@ -1,5 +1,5 @@
 """Copies of results to the caller at the sizes where the way of copying
-changes (one copy up to 2 MiB, the runtime's up to 16, a ring of chunks and
+changes (one copy up to 2 MiB, the runtime's up to 48, a ring of chunks and
 threads above), whole and with some outputs left out. At t = 0 the fields are
 the inputs to rounding (sums of nine populations: below 1e-14), and every
 value differs from its neighbours."""
@@ -24,7 +24,8 @@ def make(lx, ly):
 
 # 40 bytes a node: 26214 nodes are 1 MiB; 4 MiB chunks, 2 MiB windows
 @pytest.mark.parametrize("lx,ly", [(5, 3), (128, 64), (243, 215), (244, 215), (647, 648), (647, 649),
-                                   (1024, 512), (1013, 517), (1999, 1021)])
+                                   (1024, 512), (1228, 1024), (1230, 1024),
+                                   (1999, 1021)])
 def test_fields_at_the_sizes_where_the_copy_changes(lx, ly):
     sim, init = make(lx, ly)
     with sim:
