@@ -168,9 +168,10 @@ int tlb_init(tlb_handle **out, const tlb_params *p, const double *rho_a,
 
 /* Device bytes of the workspace tlb_init_external needs for these
  * parameters and solid flags (host, ly*lx, or NULL): both population
- * buffers, the per-block observable partials, the observables, the bottom
+ * buffers, the per-block observable partials, the bottom
  * temperature, the solid flags, the link masks and the tile list of the
- * moment steps, each part 256-byte aligned. Queries the current device (the launch geometry depends on it).
+ * moment steps, each part 256-byte aligned. Queries the current device (the
+ * launch geometry depends on it).
  * Returns the byte count, or TLB_EINVAL for invalid parameters. */
 int64_t tlb_workspace_bytes(const tlb_params *p, const uint8_t *solid);
 

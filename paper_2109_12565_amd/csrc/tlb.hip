@@ -32,7 +32,7 @@ struct tlb_handle {
   int device = 0;                  // HIP device current at tlb_init
   hipStream_t stream = nullptr;
   bool own_stream = false;
-  bool external = false;           // buf, partials, obs, t_bottom, solid, link in a
+  bool external = false;           // buf, partials, t_bottom, solid, link in a
                                    // caller's workspace (tlb_init_external)
   // the adjoint's second stream (segment recompute beside the reverse
   // sweep, default priority) and its events, created on first use
@@ -58,7 +58,6 @@ struct tlb_handle {
   uint8_t* solid = nullptr;
   void* t_bottom = nullptr;        // C-typed copy of the bottom temperature
   double* partials = nullptr;
-  double* obs = nullptr;           // [6]
   double* fields = nullptr;        // [7][ly][lx], allocated on first use
   double* rows = nullptr;          // [2][ly] row averages, allocated on first use
   // droplet detection, allocated on first use
@@ -740,7 +739,7 @@ int check_params(const tlb_params* p) {
 // observables, the bottom temperature, the solid flags, the link masks and
 // the tile list.
 struct Workspace {
-  size_t buf = 0, partials = 0, obs = 0, t_bottom = 0, solid = 0, link = 0, tiles = 0, total = 0;
+  size_t buf = 0, partials = 0, t_bottom = 0, solid = 0, link = 0, tiles = 0, total = 0;
 };
 
 Workspace workspace_layout(const tlb_params& p, size_t state_b, size_t nblocks,
@@ -750,8 +749,7 @@ Workspace workspace_layout(const tlb_params& p, size_t state_b, size_t nblocks,
   Workspace w;
   w.buf = 0;
   w.partials = 2 * up(state_b);
-  w.obs = w.partials + up(nblocks * tlbk::kObsSums * sizeof(double));
-  w.t_bottom = w.obs + up(8 * sizeof(double));
+  w.t_bottom = w.partials + up(nblocks * tlbk::kObsSums * sizeof(double));
   w.solid = w.t_bottom + up((size_t)p.lx * sizeof(double));
   w.link = w.solid + up(n);
   w.tiles = w.link + up(n * sizeof(uint16_t));
@@ -897,7 +895,6 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
     h->buf[0] = base + ws.buf;
     h->buf[1] = base + ws.buf + (ws.partials - ws.buf) / 2;
     h->partials = reinterpret_cast<double*>(base + ws.partials);
-    h->obs = reinterpret_cast<double*>(base + ws.obs);
     h->t_bottom = base + ws.t_bottom;
     h->solid = reinterpret_cast<uint8_t*>(base + ws.solid);
     if (h->has_solid) h->link = reinterpret_cast<uint16_t*>(base + ws.link);
@@ -906,7 +903,6 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
     INIT_HIP(hipMalloc(&h->buf[0], buf_bytes));
     INIT_HIP(hipMalloc(&h->buf[1], buf_bytes));
     INIT_HIP(hipMalloc(&h->partials, nblocks * tlbk::kObsSums * sizeof(double)));
-    INIT_HIP(hipMalloc(&h->obs, 8 * sizeof(double)));
     INIT_HIP(hipMalloc(&h->t_bottom, lx * (is_fp64(h) ? sizeof(double) : sizeof(float))));
     INIT_HIP(hipMalloc(&h->solid, n));
     if (h->has_solid) INIT_HIP(hipMalloc(&h->link, n * sizeof(uint16_t)));
@@ -1529,10 +1525,10 @@ int tlb_destroy(tlb_handle* h) {
     h->link = nullptr;
     h->solid = nullptr;
     h->tiles = nullptr;
-    h->partials = h->obs = nullptr;
+    h->partials = nullptr;
   }
   void* ptrs[] = {h->buf[0],   h->buf[1],     h->link,       h->solid,      h->t_bottom,
-                  h->partials, h->obs,        h->fields,     h->rows,       h->export_buf,
+                  h->partials, h->fields,     h->rows,       h->export_buf,
                   h->ckpt,     h->tape,       h->mtape,      h->adj,        h->adj_scalars,
                   h->drop_nodes, h->drop_tiles, h->drop_error, h->drop_tb,  h->drop_acc,
                   h->tiles};
