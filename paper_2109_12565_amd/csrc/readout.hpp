@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <condition_variable>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -48,7 +49,12 @@ class Readout {
       int e = k;
       while (e < parts && dst[e]) ++e;
       if (e > k) {
-        const hipError_t err = run(static_cast<const char*>(src) + k * bytes, bytes, e - k, dst + k, stream);
+        hipError_t err;
+        try {
+          err = run(static_cast<const char*>(src) + k * bytes, bytes, e - k, dst + k, stream);
+        } catch (const std::exception&) {  // no host memory for the lists; nothing was begun
+          err = hipErrorOutOfMemory;
+        }
         if (err != hipSuccess) return err;
       }
       k = e + 1;
