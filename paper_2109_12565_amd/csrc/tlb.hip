@@ -50,6 +50,8 @@ struct tlb_handle {
   // step (wall_changed); buf[0] is scratch for populations.
   bool wall_changed = false;
   bool level_valid = false;
+  bool prev_full = false;          // 16-bit storages: M(t-1) holds full values (the
+                                   // last run's last step had Device::src_full)
   tlbk::MomentTile* tiles = nullptr;  // moment steps with solid cells
   int ntiles = 0, nlinked = 0;
   int64_t t = 0;
@@ -389,21 +391,28 @@ void set_pair(tlbh::Device* d, int64_t s, int64_t n) {
   d->src_full = s > 0 && s % 2 == 0;  // (the last steps of a run: s - 1 was a pair's second)
 }
 
-void launch_moment(const tlb_handle* h, tlbh::MomentPass pass, const void* src, void* dst,
-                   double* fields = nullptr, double* partials = nullptr, int64_t step = 0,
-                   int64_t nsteps = 0) {
-  tlbh::Device d = device_view(h, fields, partials);
-  set_pair(&d, step, nsteps);
-  with_storage(h->p.precision,
+void launch_moment(const tlbh::Device& d, tlbh::MomentPass pass, const void* src, void* dst) {
+  with_storage(d.p->precision,
                [&](auto st) { tlbh::Launcher<decltype(st)>::moment(d, pass, src, dst); });
+}
+
+// A pass over moments outside a run of steps. src_full: src is a slot of full
+// values (16-bit storages; only M(t-1) can be one, see tlb_handle::prev_full).
+void launch_moment(const tlb_handle* h, tlbh::MomentPass pass, const void* src, void* dst,
+                   double* fields = nullptr, bool src_full = false) {
+  tlbh::Device d = device_view(h, fields);
+  d.src_full = src_full;
+  launch_moment(d, pass, src, dst);
 }
 
 // Step s of a run of n of the moment state.
 void moment_step(tlb_handle* h, int64_t s, int64_t n) {
-  launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, h->cur), moment_slot(h, 1 - h->cur),
-                nullptr, nullptr, s, n);
+  tlbh::Device d = device_view(h);
+  set_pair(&d, s, n);
+  launch_moment(d, tlbh::MomentPass::kStep, moment_slot(h, h->cur), moment_slot(h, 1 - h->cur));
   h->cur = 1 - h->cur;
   h->t += 1;
+  h->prev_full = d.src_full;
 }
 
 // The moments that observables and fields of time t are formed from: the
@@ -412,7 +421,8 @@ void moment_step(tlb_handle* h, int64_t s, int64_t n) {
 const void* observed_moments(tlb_handle* h) {
   if (!h->wall_changed || h->t == 0) return moment_slot(h, h->cur);
   if (!h->level_valid)  // (a run's last step, never the second of a pair)
-    launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, 1 - h->cur), moment_slot(h, 2));
+    launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, 1 - h->cur), moment_slot(h, 2), nullptr,
+                  h->prev_full);
   h->level_valid = true;
   return moment_slot(h, 2);
 }
@@ -431,7 +441,8 @@ int evaluate_time_level(tlb_handle* h, Level what, double* fields = nullptr) {
     using tlbh::MomentPass;
     if (what == Level::kStress) {
       launch_moment(h, init ? MomentPass::kPostRest : MomentPass::kPost,
-                    moment_slot(h, init ? h->cur : 1 - h->cur), h->buf[0]);
+                    moment_slot(h, init ? h->cur : 1 - h->cur), h->buf[0], nullptr,
+                    !init && h->prev_full);
       launch_pass(h, init ? Pass::kStressInit : Pass::kStress, h->buf[0], nullptr, fields);
     } else {
       launch_moment(h, what == Level::kFields ? MomentPass::kFields : MomentPass::kObserve,
@@ -1303,8 +1314,9 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
       void* dst = own;
       if (moment_tape) dst = static_cast<char*>(h->mtape) + (size_t)k * mb;
       else if (k + 1 < nsteps && (k + 1) % ckpt_every == 0) dst = ckpt(k + 1);
-      launch_moment(h, tlbh::MomentPass::kStepTopRow, src, dst, nullptr,
-                    w.loss_terms + (size_t)k * stride, k, nsteps);
+      tlbh::Device step = device_view(h, nullptr, w.loss_terms + (size_t)k * stride);
+      set_pair(&step, k, nsteps);
+      launch_moment(step, tlbh::MomentPass::kStepTopRow, src, dst);
       if (dst != own && k + 2 >= nsteps) TLB_HIP(h, copy(own, dst));
       src = dst;
       advance(1);

@@ -168,3 +168,48 @@ def test_moment_steps_are_the_fused_launches_bit_for_bit(precision, name, lanes)
         fa, fb = a.fields(), b.fields()
         for k in fa:
             assert np.array_equal(fa[k], fb[k]), (n, a.t, k)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("name", ["small", "posts"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev"])
+def test_calls_that_read_the_previous_level(precision, name, n):
+    """Stress, row averages and, under a new bottom temperature, observables,
+    fields and droplets are formed from M(t-1), whatever the number of steps
+    and the form that 16-bit storages left it in. Against the fused launches,
+    whose populations are the same bits in FP32 arithmetic: the stress terms
+    are at most 10 roundings of values below 1 (1e-6 absolute)."""
+    case = CASES[name]()
+    sims = [make(case, precision, f, u_wall=U_WALL) for f in ("auto", "always")]
+    double = precision == "fp64"
+
+    def compare(where):
+        got, ref = ((s.stress(), s.row_averages(), s.observables(), s.fields(), s.droplets(0.8, labels=True))
+                    for s in sims)
+        for k in ref[0]:
+            err = np.abs(got[0][k] - ref[0][k]).max()
+            assert err <= (1e-13 if double else 1e-6), (where, k, err)
+        for k, bar in (("u_av", 1e-13 if double else 1e-6), ("pxy_av", 1e-13 if double else 1e-6)):
+            err = np.abs(got[1][k] - ref[1][k]).max()
+            assert err <= bar, (where, k, err)
+        for k in ref[2]:
+            assert got[2][k] == pytest.approx(ref[2][k], rel=1e-12 if double else 2e-5, abs=1e-13), (where, k)
+        errs = field_errors(got[3], ref[3])
+        assert max(errs[k] for k in ("rho_a", "rho_b", "temp")) <= bars(precision)[0], (where, errs)
+        assert max(errs["ux"], errs["uy"]) <= (1e-12 if double else 2e-5), (where, errs)
+        for k in ("root", "size", "label"):
+            assert np.array_equal(got[4][k], ref[4][k]), (where, k)
+
+    print(precision, name, n, flush=True)
+    for s in sims:
+        s.step(n)
+    compare("as stepped")
+    for s in sims:
+        s.set_bottom_temperature(1.3 * case["t_bottom"])
+    compare("new bottom temperature")
+    for s in sims:
+        s.step(0)
+    compare("after no step")
+    for s in sims:
+        s.step(n + 1)
+    compare("stepped on")
