@@ -45,11 +45,10 @@ struct tlb_handle {
   void* buf[2] = {nullptr, nullptr};
   int cur = 0;                     // buf[cur] = f*(t); buf[1-cur] = f*(t-1) or f(0)
   // Moment state (launch.rows_m > 0): buf[1] holds the moments M(t) in slot
-  // `cur` (0 or 1), M(t-1) in slot 1 - cur, and in slot 2, when
-  // level_valid, M(t) pulled again under a bottom temperature set after the
-  // step (wall_changed); buf[0] is scratch for populations.
+  // `cur` (0 or 1), M(t-1) in slot 1 - cur, and slot 2 takes M(t) pulled again
+  // under a bottom temperature set after the step (wall_changed); buf[0] is
+  // scratch for populations.
   bool wall_changed = false;
-  bool level_valid = false;
   bool prev_full = false;          // 16-bit storages: M(t-1) holds full values (the
                                    // last run's last step had Device::src_full)
   tlbk::MomentTile* tiles = nullptr;  // moment steps with solid cells
@@ -417,13 +416,13 @@ void moment_step(tlb_handle* h, int64_t s, int64_t n) {
 
 // The moments that observables and fields of time t are formed from: the
 // state's, or, after a new bottom temperature, those of the same step pulled
-// under it.
-const void* observed_moments(tlb_handle* h) {
+// under it (a run's last step, never the second of a pair). Pulled at every
+// call: a HIP graph of tlb_step that the caller replays moves the state on
+// without the handle's knowing.
+const void* observed_moments(const tlb_handle* h) {
   if (!h->wall_changed || h->t == 0) return moment_slot(h, h->cur);
-  if (!h->level_valid)  // (a run's last step, never the second of a pair)
-    launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, 1 - h->cur), moment_slot(h, 2), nullptr,
-                  h->prev_full);
-  h->level_valid = true;
+  launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, 1 - h->cur), moment_slot(h, 2), nullptr,
+                h->prev_full);
   return moment_slot(h, 2);
 }
 
@@ -1008,7 +1007,7 @@ int tlb_step(tlb_handle* h, int64_t nsteps) {
   if (nsteps < 0) return fail(h, TLB_EINVAL, "tlb_step: nsteps < 0");
   if (has_moments(h)) {
     for (int64_t s = 0; s < nsteps; ++s) moment_step(h, s, nsteps);
-    if (nsteps > 0) h->wall_changed = h->level_valid = false;
+    if (nsteps > 0) h->wall_changed = false;
     TLB_HIP(h, hipGetLastError());
     return TLB_OK;
   }
@@ -1054,9 +1053,10 @@ int tlb_launch_info(const tlb_handle* h, tlb_launch* out) {
 int tlb_observables(tlb_handle* h, tlb_obs* out) {
   if (!h || !out) return fail(h, TLB_EINVAL, "tlb_observables: NULL argument");
   // the last population step of tlb_step left the sums of the current time;
-  // otherwise (the moment state, a taped run, a new bottom temperature)
-  // evaluate the time level
-  if (h->obs_t != h->t) {
+  // otherwise (a taped run, a new bottom temperature) evaluate the time level.
+  // The moment state's steps leave none, so it is always evaluated there: the
+  // state may have moved on in a replayed HIP graph of tlb_step.
+  if (has_moments(h) || h->obs_t != h->t) {
     int rc = evaluate_time_level(h, Level::kObserve);
     if (rc != TLB_OK) return rc;
     h->obs_t = h->t;
@@ -1216,7 +1216,6 @@ int tlb_set_bottom_temperature(tlb_handle* h, const double* t_bottom) {
   h->tape_valid = false;
   h->obs_t = -1;
   h->wall_changed = true;
-  h->level_valid = false;
   h->host_tb.assign(t_bottom, t_bottom + lx);
   h->dtdy_sum = dtdy_sum(h);
   if (is_fp64(h)) {
@@ -1321,7 +1320,7 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
       src = dst;
       advance(1);
     }
-    h->wall_changed = h->level_valid = false;
+    h->wall_changed = false;
   } else if (moment_tape) {
     auto mslot = [&](int64_t k) { return static_cast<char*>(h->mtape) + (size_t)k * moment_bytes(h); };
     int64_t k = 0;
