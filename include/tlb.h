@@ -201,7 +201,10 @@ int tlb_init_external(tlb_handle **out, const tlb_params *p, const double *rho_a
  * pairs of steps may run as one fused launch where the handle's storage and
  * lattice allow it (see tlb_launch_info; flat walls at rest or moving, posts
  * allowed); the last step of a call is then a single step, which also forms
- * the observable sums of the new time. Results agree with single population
+ * the observable sums of the new time. A moment handle's calls of two and more
+ * steps, and pairs of calls of one, leave the state where it was in memory: a
+ * HIP graph that captured them advances it at every replay (tlb_time does not
+ * see replays). Results agree with single population
  * steps to rounding either way. Returns TLB_EINVAL for nsteps < 0 or a
  * NULL handle, TLB_EDEVICE on a launch failure. */
 int tlb_step(tlb_handle *h, int64_t nsteps);

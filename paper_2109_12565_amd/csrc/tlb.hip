@@ -44,10 +44,11 @@ struct tlb_handle {
   size_t elem = 0;                 // bytes per stored population value
   void* buf[2] = {nullptr, nullptr};
   int cur = 0;                     // buf[cur] = f*(t); buf[1-cur] = f*(t-1) or f(0)
-  // Moment state (launch.rows_m > 0): buf[1] holds the moments M(t) in slot
-  // `cur` (0 or 1), M(t-1) in slot 1 - cur, and slot 2 takes M(t) pulled again
-  // under a bottom temperature set after the step (wall_changed); buf[0] is
+  // Moment state (launch.rows_m > 0): buf[1] has three slots, of which `cur`
+  // holds the moments M(t) and `prev` M(t-1); the third takes M(t) pulled again
+  // under a bottom temperature set after the step (wall_changed). buf[0] is
   // scratch for populations.
+  int prev = 1;
   bool wall_changed = false;
   bool prev_full = false;          // 16-bit storages: M(t-1) holds full values (the
                                    // last run's last step had Device::src_full)
@@ -378,7 +379,7 @@ size_t moment_bytes(const tlb_handle* h) {
 
 bool has_moments(const tlb_handle* h) { return h->launch.rows_m > 0; }
 
-// Slot k of the moment state (buf[1] holds five).
+// Slot k of the moment state.
 void* moment_slot(const tlb_handle* h, int k) {
   return static_cast<char*>(h->buf[1]) + (size_t)k * moment_bytes(h);
 }
@@ -404,14 +405,22 @@ void launch_moment(const tlb_handle* h, tlbh::MomentPass pass, const void* src, 
   launch_moment(d, pass, src, dst);
 }
 
-// Step s of a run of n of the moment state.
-void moment_step(tlb_handle* h, int64_t s, int64_t n) {
-  tlbh::Device d = device_view(h);
-  set_pair(&d, s, n);
-  launch_moment(d, tlbh::MomentPass::kStep, moment_slot(h, h->cur), moment_slot(h, 1 - h->cur));
-  h->cur = 1 - h->cur;
-  h->t += 1;
-  h->prev_full = d.src_full;
+// A run of n steps of the moment state. From two steps on it ends in the slot
+// it began in (an odd run goes through the third one once), so that a HIP graph
+// of it can be replayed.
+void moment_run(tlb_handle* h, int64_t n) {
+  const int first = h->cur, second = h->prev, third = 3 - first - second;
+  for (int64_t s = 0; s < n; ++s) {
+    tlbh::Device d = device_view(h);
+    set_pair(&d, s, n);
+    const int dst = h->cur == first ? second : s == 1 && n % 2 == 1 ? third : first;
+    launch_moment(d, tlbh::MomentPass::kStep, moment_slot(h, h->cur), moment_slot(h, dst));
+    h->prev = h->cur;
+    h->cur = dst;
+    h->t += 1;
+    h->prev_full = d.src_full;
+  }
+  if (n > 0) h->wall_changed = false;
 }
 
 // The moments that observables and fields of time t are formed from: the
@@ -421,9 +430,9 @@ void moment_step(tlb_handle* h, int64_t s, int64_t n) {
 // without the handle's knowing.
 const void* observed_moments(const tlb_handle* h) {
   if (!h->wall_changed || h->t == 0) return moment_slot(h, h->cur);
-  launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, 1 - h->cur), moment_slot(h, 2), nullptr,
-                h->prev_full);
-  return moment_slot(h, 2);
+  void* again = moment_slot(h, 3 - h->cur - h->prev);
+  launch_moment(h, tlbh::MomentPass::kStep, moment_slot(h, h->prev), again, nullptr, h->prev_full);
+  return again;
 }
 
 // Re-run the step that produced f*(t) without storing, to evaluate the
@@ -440,7 +449,7 @@ int evaluate_time_level(tlb_handle* h, Level what, double* fields = nullptr) {
     using tlbh::MomentPass;
     if (what == Level::kStress) {
       launch_moment(h, init ? MomentPass::kPostRest : MomentPass::kPost,
-                    moment_slot(h, init ? h->cur : 1 - h->cur), h->buf[0], nullptr,
+                    moment_slot(h, init ? h->cur : h->prev), h->buf[0], nullptr,
                     !init && h->prev_full);
       launch_pass(h, init ? Pass::kStressInit : Pass::kStress, h->buf[0], nullptr, fields);
     } else {
@@ -1006,8 +1015,7 @@ int tlb_step(tlb_handle* h, int64_t nsteps) {
   if (!h) return fail(nullptr, TLB_EINVAL, "tlb_step: NULL handle");
   if (nsteps < 0) return fail(h, TLB_EINVAL, "tlb_step: nsteps < 0");
   if (has_moments(h)) {
-    for (int64_t s = 0; s < nsteps; ++s) moment_step(h, s, nsteps);
-    if (nsteps > 0) h->wall_changed = false;
+    moment_run(h, nsteps);
     TLB_HIP(h, hipGetLastError());
     return TLB_OK;
   }
@@ -1309,7 +1317,8 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
     const void* src = moment_slot(h, h->cur);   // M(t0 + k)
     if (!moment_tape) TLB_HIP(h, copy(ckpt(0), src));
     for (int64_t k = 0; k < nsteps; ++k) {
-      void* own = moment_slot(h, 1 - h->cur);
+      const int next = h->cur == 0 ? 1 : 0;
+      void* own = moment_slot(h, next);
       void* dst = own;
       if (moment_tape) dst = static_cast<char*>(h->mtape) + (size_t)k * mb;
       else if (k + 1 < nsteps && (k + 1) % ckpt_every == 0) dst = ckpt(k + 1);
@@ -1318,7 +1327,9 @@ int tlb_forward_taped(tlb_handle* h, int64_t nsteps, int32_t ckpt_every, double*
       launch_moment(step, tlbh::MomentPass::kStepTopRow, src, dst);
       if (dst != own && k + 2 >= nsteps) TLB_HIP(h, copy(own, dst));
       src = dst;
-      advance(1);
+      h->prev = h->cur;
+      h->cur = next;
+      h->t += 1;
     }
     h->wall_changed = false;
   } else if (moment_tape) {

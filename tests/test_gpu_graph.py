@@ -33,7 +33,7 @@ def same(a, b, where):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev"])
-@pytest.mark.parametrize("n", [2, 4, 6])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6, 7])
 def test_replayed_steps_are_observed_afresh(precision, n):
     case = posts_case()
     print(precision, n, flush=True)
