@@ -26,6 +26,7 @@ struct Geometry {
   int strip_m = 0;   // stored columns per wavefront
   dim3 grid_m;       // strips x chunks, one wavefront each
   int slots_m = 0;   // wavefronts the chunks are cut for
+  int simds_m = 0;   // SIMDs of the device
 };
 
 // Lanes per block of the two-step kernel (wide and narrow blocks) and the

@@ -42,6 +42,7 @@
 #include <utility>
 
 #include "lb_kernels.hpp"
+#include "moment_tiles.hpp"
 
 namespace tlbk {
 
@@ -62,12 +63,6 @@ enum : unsigned {
 // column needs equilibria within 1, whose forces need psi within 2 more.
 constexpr int kMomHalo = 3;
 constexpr int kMomStrip = 64 - 2 * kMomHalo;
-
-// Rows y0 .. y1 - 1 of one strip. `linked`: some stored node has a solid link
-// other than those of the flat walls.
-struct MomentTile {
-  int strip, y0, y1, linked;
-};
 
 template <typename C>
 struct MomentArgs {

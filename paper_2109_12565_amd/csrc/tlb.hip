@@ -276,70 +276,21 @@ tlbh::Geometry choose_launch(const tlb_params& p, size_t buffer_bytes, bool soli
     const bool one = p.precision == TLB_FP64 && rows_for(1) <= 20;
     const long long rows_m = p.rows > 0 ? p.rows : rows_for(one ? 1 : 2);
     l.rows_m = (int)std::min<long long>(rows_m, ly);
-    l.slots_m = (int)(cus * kSimds * (one ? 1 : 2));
+    l.simds_m = (int)(cus * kSimds);
+    l.slots_m = l.simds_m * (one ? 1 : 2);
     l.strip_m = (int)((lx + strips_m - 1) / strips_m);
     l.grid_m = dim3((unsigned)strips_m, (unsigned)((ly + l.rows_m - 1) / l.rows_m), 1);
   }
   return l;
 }
 
-// Tiles of the moment step where solid cells exist. A row of a strip is
-// linked where a stored node's mask is not the flat walls' one; runs of linked
-// rows (with gaps of up to three others) are cut into tiles of half the
-// launch's chunk height (at most 8 rows: a linked row takes longer), the rest
-// into tiles of the chunk height, or the one at which all are resident at once.
+// Tiles of the moment step of a lattice with solid cells.
 std::vector<tlbk::MomentTile> moment_tiles(const tlb_params& p, const tlbh::Geometry& g,
                                            const std::vector<uint16_t>& link, int* nlinked) {
-  const int lx = p.lx, ly = p.ly;
-  const int strips = (int)g.grid_m.x;
-  std::vector<tlbk::MomentTile> linked, plain;
-  auto cut = [](std::vector<tlbk::MomentTile>& to, int strip, int y0, int y1, int most, int flag) {
-    const int n = (y1 - y0 + most - 1) / most;
-    for (int k = 0; k < n; ++k)
-      to.push_back({strip, y0 + (int)((long long)(y1 - y0) * k / n),
-                    y0 + (int)((long long)(y1 - y0) * (k + 1) / n), flag});
-  };
-  std::vector<tlbk::MomentTile> runs;  // of rows without links
-  std::vector<char> marked((size_t)ly);
-  for (int s = 0; s < strips; ++s) {
-    const int x0 = s * g.strip_m, x1 = std::min(x0 + g.strip_m, lx);
-    for (int y = 0; y < ly; ++y) {
-      const uint32_t flat = (y == 0 ? tlbk::kFromBelow : 0u) | (y == ly - 1 ? tlbk::kFromAbove : 0u);
-      const uint16_t* row = link.data() + (size_t)y * lx;
-      marked[y] = std::any_of(row + x0, row + x1, [&](uint16_t m) { return m != flat; });
-    }
-    for (int y = 0; y < ly;) {
-      int e = y;
-      if (marked[y]) {
-        for (int k = y; k < ly && k < e + 4; ++k)
-          if (marked[k]) e = k + 1;
-        cut(linked, s, y, e, std::min(8, std::max(1, g.rows_m / 2)), 1);
-      } else {
-        while (e < ly && !marked[e]) ++e;
-        runs.push_back({s, y, e, 0});
-      }
-      y = e;
-    }
-  }
-  int rows = g.rows_m;
-  if (p.rows == 0) {
-    const long long room = std::max<long long>(1, g.slots_m - (long long)linked.size());
-    auto count = [&](int h) {
-      long long n = 0;
-      for (const auto& t : runs) n += (t.y1 - t.y0 + h - 1) / h;
-      return n;
-    };
-    while (rows < ly && count(rows) > std::max<long long>(room, (long long)runs.size())) ++rows;
-  }
-  for (const auto& t : runs) cut(plain, t.strip, t.y0, t.y1, rows, 0);
-  // strip fastest: neighbouring strips at the same height run together
-  std::stable_sort(plain.begin(), plain.end(),
-                   [](const auto& u, const auto& v) { return u.y0 < v.y0; });
-  std::stable_sort(linked.begin(), linked.end(),
-                   [](const auto& u, const auto& v) { return u.y0 < v.y0; });
-  *nlinked = (int)linked.size();
-  linked.insert(linked.end(), plain.begin(), plain.end());
-  return linked;
+  const tlbk::MomentTileRule rule{p.lx,        p.ly,      (int)g.grid_m.x,  g.strip_m,
+                                  g.rows_m,    p.rows > 0, g.slots_m,       g.simds_m,
+                                  tlbk::kFromBelow, tlbk::kFromAbove};
+  return tlbk::moment_tiles(rule, link.data(), nlinked);
 }
 
 tlbh::Device device_view(const tlb_handle* h, double* fields = nullptr,
