@@ -92,8 +92,10 @@ enum class MomentPass {
   kObserve,     // observable sums of time t into partials
   kFields,      // fields of time t
   kExport,      // f*(t) as doubles [27][ly][lx] into dst
-  kPost,        // f*(t) in the population layout into dst
-  kPostRest     // f(0) from M(0) in the population layout into dst
+  kShear,       // xy moments of f_A(t+1) and f_B(t+1) as pulled from f*(t), [2]
+                // planes into dst
+  kStress       // u_x and xy stress of time t into the fields; dst: the planes
+                // of kShear from M(t-1), or at t = 0 of init_moments
 };
 
 template <class St>
@@ -112,9 +114,11 @@ struct Launcher {
                                const double* temp, const double* ux0, const double* uy0);
   static void export_populations(const Device& d, const void* buf, double* out);
   static void moment(const Device& d, MomentPass pass, const void* src, void* dst);
-  // M(0) from the initial fields (the velocities may be null).
-  static void init_moments(const Device& d, void* dst, const double* rho_a, const double* rho_b,
-                           const double* temp, const double* ux0, const double* uy0);
+  // M(0) and the xy moments of f(0) ([2] planes) from the initial fields (the
+  // velocities may be null).
+  static void init_moments(const Device& d, void* dst, void* shear, const double* rho_a,
+                           const double* rho_b, const double* temp, const double* ux0,
+                           const double* uy0);
 };
 
 // Work buffers of the reverse sweep, in the compute type of the storage and

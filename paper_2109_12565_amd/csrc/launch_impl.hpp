@@ -185,7 +185,7 @@ void launch_moment_solid(const Device& d, const tlbk::MomentArgs<typename St::C>
 
 template <class St, unsigned kMode>
 void launch_moment_split(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
-  if constexpr (tlbk::kSameRounding<typename St::C>) {
+  if constexpr (tlbk::kSameRounding<typename St::C> && (kMode & tlbk::kMomShear) == 0) {
     if (d.pair_second) {
       launch_moment_kernel<St, kMode | tlbk::kMomSplit>(d, a);
       return;
@@ -194,9 +194,9 @@ void launch_moment_split(const Device& d, const tlbk::MomentArgs<typename St::C>
   launch_moment_kernel<St, kMode>(d, a);
 }
 
-template <class St>
-void launch_moment_step(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
-  constexpr unsigned M = tlbk::kMomStep, S = tlbk::kModeSolid, V = tlbk::kModeMoving;
+template <class St, unsigned M>
+void launch_moment_walls(const Device& d, const tlbk::MomentArgs<typename St::C>& a) {
+  constexpr unsigned S = tlbk::kModeSolid, V = tlbk::kModeMoving;
   if (d.moving) {
     if (d.has_solid) launch_moment_split<St, M | S | V>(d, a);
     else launch_moment_split<St, M | V>(d, a);
@@ -238,15 +238,18 @@ void launch_moment(const Device& d, MomentPass pass, const void* src, void* dst)
   }
   a.x2 = C((double)a.s.g12 * w(2) * (double)a.s.inv_rho0 * (double)a.s.inv_rho0);
   switch (pass) {
-    case MomentPass::kStep: launch_moment_step<St>(d, a); break;
+    case MomentPass::kStep: launch_moment_walls<St, kMomStep>(d, a); break;
     case MomentPass::kStepTopRow:  // the adjoint's
       if constexpr (kHasAdjoint<St>) launch_moment_split<St, kMomStep | kModeTopRow>(d, a);
       break;
     case MomentPass::kObserve: launch_moment_solid<St, kMomObserve>(d, a); break;
     case MomentPass::kFields: launch_moment_solid<St, kMomFields>(d, a); break;
     case MomentPass::kExport: launch_moment_solid<St, kMomExport>(d, a); break;
-    case MomentPass::kPost: launch_moment_solid<St, kMomPost>(d, a); break;
-    case MomentPass::kPostRest: launch_moment_solid<St, kMomPost | kMomRest>(d, a); break;
+    case MomentPass::kShear: launch_moment_walls<St, kMomStep | kMomShear>(d, a); break;
+    case MomentPass::kStress:
+      a.shear = static_cast<const C*>(dst);
+      launch_moment_solid<St, kMomFields | kMomStress>(d, a);
+      break;
   }
 }
 
@@ -344,7 +347,7 @@ void Launcher<St>::moment(const Device& d, MomentPass pass, const void* src, voi
 }
 
 template <class St>
-void Launcher<St>::init_moments(const Device& d, void* dst, const double* rho_a,
+void Launcher<St>::init_moments(const Device& d, void* dst, void* shear, const double* rho_a,
                                 const double* rho_b, const double* temp, const double* ux0,
                                 const double* uy0) {
   if constexpr (detail::kHasMoments<St>) {
@@ -352,8 +355,8 @@ void Launcher<St>::init_moments(const Device& d, void* dst, const double* rho_a,
     const tlb_params& p = *d.p;
     dim3 grid((p.lx + 255) / 256, p.ly, 1);
     hipLaunchKernelGGL(tlbk::lb_moment_init<St>, grid, dim3(256), 0, d.stream,
-                       static_cast<C*>(dst), rho_a, rho_b, temp, ux0, uy0, d.solid, p.lx, d.pitch,
-                       d.pop_stride, C(p.rho_wall[0]), C(p.rho_wall[1]), C(p.rho_ref[0]),
+                       static_cast<C*>(dst), static_cast<C*>(shear), rho_a, rho_b, temp, ux0, uy0,
+                       d.solid, p.lx, d.pitch, d.pop_stride, C(p.rho_wall[0]), C(p.rho_wall[1]), C(p.rho_ref[0]),
                        C(p.rho_ref[1]), C(p.t_ref));
   }
 }

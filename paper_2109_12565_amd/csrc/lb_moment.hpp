@@ -53,10 +53,14 @@ enum : unsigned {
   kMomObserve = 2u << 16, // observable sums of time t into partials
   kMomFields = 4u << 16,  // fields of time t
   kMomExport = 8u << 16,  // f*(t) as doubles [27][ly][lx], zero at solid nodes
-  kMomPost = 16u << 16,   // f*(t) in the population layout
-  kMomRest = 32u << 16,   // with kMomPost: no force enters (f(0) from M(0))
-  kMomSplit = 64u << 16   // FP32 steps: populations rounded as between the two
+  kMomShear = 16u << 16,  // with kMomStep: the xy moments of the populations of
+                          // f_A and f_B pulled at time t + 1, two planes, in
+                          // place of M(t + 1)
+  kMomSplit = 32u << 16,  // FP32 steps: populations rounded as between the two
                           // levels of a fused launch (see equilibria_same)
+  kMomStress = 64u << 16  // with kMomFields: u_x and the xy stress of time t
+                          // (field planes 2, 5 and 6) from M(t) and the xy
+                          // moments of f(t)
 };
 
 // Columns of a wavefront that only feed the others, on each side: a stored
@@ -66,9 +70,10 @@ constexpr int kMomStrip = 64 - 2 * kMomHalo;
 
 template <typename C>
 struct MomentArgs {
-  StepArgs<C> s;  // src, dst: moment planes [5][pop_stride] (dst of kMomPost:
-                  // population planes); partials; fields
+  StepArgs<C> s;  // src, dst: moment planes [5][pop_stride] (kMomShear: dst
+                  // [2][pop_stride]); partials; fields
   double* out;    // kMomExport: [27][ly][lx]
+  const C* shear; // kMomStress: the xy moments, [2][pop_stride]
   int strip;      // stored columns per wavefront (at most kMomStrip)
   const MomentTile* tiles;  // steps with solid cells: the wavefronts' tiles,
   int ntiles, nlinked;      // the nlinked first ones hold solid links
@@ -274,6 +279,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   constexpr bool kSolid = (kMode & kModeSolid) != 0;
   constexpr bool kStep = (kMode & kMomStep) != 0;
   constexpr bool kTop = (kMode & kModeTopRow) != 0;
+  constexpr bool kShear = (kMode & kMomShear) != 0, kStress = (kMode & kMomStress) != 0;
   const StepArgs<C>& a = ma.s;
   const int lx = a.lx, ly = a.ly;
   const int lane = threadIdx.x;
@@ -312,7 +318,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   [[maybe_unused]] C raw[R][2];       // kDev: densities as loaded
   C psi[R][2], dpx[R][2], drx[R][2];  // psi and the x-differences of psi and rho
   constexpr bool kSame = kSameRounding<C>, kSplit = (kMode & kMomSplit) != 0;
-  [[maybe_unused]] C dp2[R][2];       // kSame: psi(x + 2) - psi(x - 2)
+  [[maybe_unused]] C dp2[R][2];       // kSame, kStress: psi(x + 2) - psi(x - 2)
   C v1[2] = {0, 0};                  // rho(q + 1) - rho(q - 1)
   // Carried from row q - 1 (= d), per field (f_A, f_B, g): what row d has
   // pulled from rows d - 1 and d, before the shift between lanes: from the
@@ -323,7 +329,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   // momentum bounced back at row d (the y part is in um2).
   C pc[3] = {0, 0, 0}, pl[3] = {0, 0, 0}, pr[3] = {0, 0, 0};
   C up[3][3] = {}, um2[2] = {0, 0}, um5 = 0, um6 = 0, jx_own = 0;
-  // The same in kSame, where sums keep the population kernels' order: cp the
+  // The same in kSame and kShear, where sums keep the population kernels' order: cp the
   // sum of directions 0..3 pulled at row d, c2, c5, c6 its upward ones, e13 the
   // difference of 1 and 3; up holds the shifted raw ones.
   [[maybe_unused]] C cp[3] = {0, 0, 0}, c2[2] = {0, 0}, c5[3] = {0, 0, 0}, c6[3] = {0, 0, 0};
@@ -363,6 +369,13 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
     mdst.put(o + 4 * plane_b, vout, solid ? C(0) : n[2]);
   };
 
+  // xy moments of row d's populations (nothing reads those of solid nodes)
+  [[maybe_unused]] auto put_shear = [&](int d, const C (&pi)[2]) {
+    const uint32_t o = (uint32_t)d * row_b;
+    mdst.put(o, vout, pi[0]);
+    mdst.put(o + plane_b, vout, pi[1]);
+  };
+
   // One iteration. kPsi: only row r's own part (the first four rows of a
   // chunk); kInner: rows r + kAhead .. d inside the lattice and the chunk and no
   // solid link in rows q and d, so no test of a row or a link is left and the
@@ -387,7 +400,9 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
         dp2[S][l] = from_right(right) - from_left(left);
       } else {
         psi[S][l] = psi_moment(rho[S][l], a.rho0, a.inv_rho0);
-        dpx[S][l] = from_right(psi[S][l]) - from_left(psi[S][l]);
+        const C left = from_left(psi[S][l]), right = from_right(psi[S][l]);
+        dpx[S][l] = right - left;
+        if constexpr (kStress) dp2[S][l] = from_right(right) - from_left(left);
       }
       drx[S1][l] = from_right(rho[S1][l]) - from_left(rho[S1][l]);
       v1n[l] = rho[S][l] - rho[Q][l];
@@ -488,6 +503,31 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
               acc[4] += (double)hx * (double)hx + (double)hy * (double)hy;
               if (q == ly - 1) acc[5] += dt - (double)a.t_top;
             }
+          } else if constexpr (kStress) {
+            // -(1 - 1/(2 tau)) (sum c_x c_y f - rho u_x u_y) of both components,
+            // and the interaction pressure: nodes at +-c share c_x c_y, so
+            // differences across columns, differenced over the rows
+            const size_t nn = (size_t)lx * ly, o = (size_t)q * lx + xl;
+            const C* pi = ma.shear + (size_t)q * a.pitch + xl;
+            const C ux = mx[Q] * inv_rho, uy = my[Q] * inv_rho;
+            C visc = 0, pint = 0;
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+              const C* F = l == 0 ? FA : FB;
+              const int m = 1 - l;
+              const C rl = rho[Q][l], t = recip_moment<St>(rl);
+              const C vx = fma(F[0], t, ux), vy = fma(F[1], t, uy);
+              visc += fma(-(rl * vx), vy, pi[(size_t)l * a.pop_stride]);
+              const C d1 = dpx[S1][l] - dpx[S3][l], d2 = dp2[S][l] - dp2[S4][l];
+              const C d12 = (dpx[S][l] - dpx[S4][l]) + (dp2[S1][l] - dp2[S3][l]);
+              const C self = fma(C(2) * ma.h8[l], d2, fma(ma.h5[l], d12, ma.g2[l] * d1));
+              const C cross = w_c2<C>(2) * (drx[S1][m] - drx[S3][m]);
+              const C pre = C(0.5) * a.g12 * a.inv_rho0 * a.inv_rho0 * rl;
+              pint += fma(pre, cross, C(0.5) * psi[Q][l] * self);
+            }
+            a.fields[2 * nn + o] = solid ? 0.0 : (double)hx;
+            a.fields[5 * nn + o] = solid ? 0.0 : (double)(C(-0.5) * visc);
+            a.fields[6 * nn + o] = solid ? 0.0 : (double)pint;
           } else {
             const size_t nn = (size_t)lx * ly, o = (size_t)q * lx + xl;
             double tv = dt;
@@ -507,16 +547,11 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
       }
       const C k = kSame ? inv_rho : inv_rho * C(kVelScale);
       const C ux = mx[Q] * k, uy = my[Q] * k;
-      if constexpr ((kMode & kMomRest) != 0) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) vx[i] = ux, vy[i] = uy;
-      } else {
-        const C scale = kSame ? C(1) : C(kVelScale);
-        const C tA = recip_moment<St>(ra) * scale, tB = recip_moment<St>(rb) * scale;
-        vx[0] = fma(FA[0], tA, ux), vy[0] = fma(FA[1], tA, uy);
-        vx[1] = fma(FB[0], tB, ux), vy[1] = fma(FB[1], tB, uy);
-        vx[2] = fma(C(0.5) * Fx, k, ux), vy[2] = fma(C(0.5) * Fy, k, uy);
-      }
+      const C scale = kSame ? C(1) : C(kVelScale);
+      const C tA = recip_moment<St>(ra) * scale, tB = recip_moment<St>(rb) * scale;
+      vx[0] = fma(FA[0], tA, ux), vy[0] = fma(FA[1], tA, uy);
+      vx[1] = fma(FB[0], tB, ux), vy[1] = fma(FB[1], tB, uy);
+      vx[2] = fma(C(0.5) * Fx, k, ux), vy[2] = fma(C(0.5) * Fy, k, uy);
     }
     v1[0] = v1n[0];
     v1[1] = v1n[1];
@@ -524,38 +559,28 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
     [[maybe_unused]] C dev[3] = {0, 0, 0};  // deviation storages
     if constexpr (kDev)
       dev[0] = raw[Q][0] + to_dev[0], dev[1] = raw[Q][1] + to_dev[1], dev[2] = tt[Q] + to_dev[2];
-    if constexpr ((kMode & (kMomExport | kMomPost)) != 0) {
+    auto populations = [&](auto kc, C (&f)[9]) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (kDev && !kSplit) equilibria_stored<St>(dens[k], dev[k], ref[k], vx[k], vy[k], f);
+      else if constexpr (kSame) equilibria_same<kSplit>(dens[k], vx[k], vy[k], f);
+      else equilibria(dens[k], vx[k], vy[k], f);
+    };
+    if constexpr ((kMode & kMomExport) != 0) {
       if (!out_lane || q >= y1) return;
       const bool solid = kSolid && !kIn && (lq & kSelfSolid) != 0;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
+      unroll<3>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
         C f[9];
-        if constexpr (kDev) equilibria_stored<St>(dens[k], dev[k], ref[k], vx[k], vy[k], f);
-        else if constexpr (kSame) equilibria_same<false>(dens[k], vx[k], vy[k], f);
-        else equilibria(dens[k], vx[k], vy[k], f);
+        populations(kc, f);
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
-          if constexpr ((kMode & kMomExport) != 0) {
-            const double v = kDev ? fma(w_dir<double>(i), (double)ref[k], (double)f[i]) : (double)f[i];
-            ma.out[((size_t)(9 * k + i) * ly + q) * lx + xl] = solid ? 0.0 : v;
-          } else if constexpr (kDev) {  // in the storage's layout, rest planes last
-            using T = typename St::T;
-            static_assert(St::kRest32, "FP32 rest planes");
-            T* to = static_cast<T*>(a.dst);
-            const size_t o = (size_t)q * a.pitch + xl;
-            if (i == 0)
-              (reinterpret_cast<float*>(to + (size_t)27 * a.pop_stride) + (size_t)k * a.pop_stride)[o] =
-                  solid ? 0.0f : f[i];
-            else
-              to[(size_t)(9 * k + i) * a.pop_stride + o] = St::encode(solid ? C(0) : f[i]);
-          } else
-            static_cast<C*>(a.dst)[(size_t)(9 * k + i) * a.pop_stride + (size_t)q * a.pitch + xl] =
-                solid ? C(0) : f[i];
+          const double v = kDev ? fma(w_dir<double>(i), (double)ref[k], (double)f[i]) : (double)f[i];
+          ma.out[((size_t)(9 * k + i) * ly + q) * lx + xl] = solid ? 0.0 : v;
         }
-      }
+      });
       return;
     }
-    if constexpr (kStep && kSame) {
+    if constexpr (kStep && (kSame || kShear)) {
       // Field by field. Row d = q - 1 pulls its downward populations from row
       // q, or, across a solid link, takes its own upward ones (opposite
       // direction; 2 w T_w minus them for g), and is complete; row q starts
@@ -565,12 +590,12 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
       const bool back_d = kSolid && !kIn && __any((lm_d & kFromAbove) != 0u);
       const bool back_q = !kIn && (kSolid ? __any((lq & kLinkBits & ~kFromAbove) != 0u) : q == 0);
       C n[3], jx = 0, jy = 0;
+      [[maybe_unused]] C pi[2];
       auto field = [&](auto kc) {
         constexpr int k = decltype(kc)::value;
         constexpr bool kG = k == 2;
         C f[9];
-        if constexpr (kDev && !kSplit) equilibria_stored<St>(dens[k], dev[k], ref[k], vx[k], vy[k], f);
-        else equilibria_same<kSplit>(dens[k], vx[k], vy[k], f);
+        populations(kc, f);
         // the value v of direction I, bounced where the link of row `row` is
         // solid: `own` is the node's population of the opposite direction
         auto bounce = [&](auto ic, C& v, C own, uint32_t links, int row) {
@@ -594,6 +619,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
           bounce(std::integral_constant<int, 7>{}, d7, own5, lm_d, d);
           bounce(std::integral_constant<int, 8>{}, d8, own6, lm_d, d);
         }
+        if constexpr (kShear) pi[k] = (c5[k] + d7) - (c6[k] + d8);
         n[k] = (cp[k] + ((d4 + c5[k]) + (c6[k] + d7))) + d8;
         if constexpr (!kG) {
           const C e57 = c5[k] - d7;
@@ -629,8 +655,11 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
         }
         up[k][0] = f[2], up[k][1] = from_left(f[5]), up[k][2] = from_right(f[6]);
       };
-      unroll<3>(field);
-      if (kIn || d >= y0) put_row(d, n, jx, jy);
+      unroll<kShear ? 2 : 3>(field);
+      if (kIn || d >= y0) {
+        if constexpr (kShear) put_shear(d, pi);
+        else put_row(d, n, jx, jy);
+      }
       lm_d = lq;
     } else if constexpr (kStep) {
       // Field by field. Row d = q - 1 pulls its downward populations from row
@@ -744,9 +773,10 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   if constexpr (kStep) {
     if (y1 == ly) {  // the top row is complete: nothing comes down to it
       C n[3], jx = 0, jy = 0;
-      if constexpr (kSame) {
+      [[maybe_unused]] C pi[2];
+      if constexpr (kSame || kShear) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
+        for (int k = 0; k < (kShear ? 2 : 3); ++k) {
           C d4 = up[k][0], d7 = from_right(up[k][1]), d8 = from_left(up[k][2]);
           if (k == 2) {
             constexpr C wa = C(2) * w_dir<C>(4), wd = C(2) * w_dir<C>(7);
@@ -761,6 +791,7 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
             d8 = fma(m, top_rho[k], d8);
             d7 = fma(-m, top_rho[k], d7);
           }
+          if constexpr (kShear) pi[k] = (c5[k] + d7) - (c6[k] + d8);
           n[k] = (cp[k] + ((d4 + c5[k]) + (c6[k] + d7))) + d8;
           if (k < 2) {
             const C e57 = c5[k] - d7;
@@ -778,7 +809,8 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
         }
         jy = (um2[0] + um2[1]) + (from_left(um5) + from_right(um6));
       }
-      put_row(ly - 1, n, jx, jy);
+      if constexpr (kShear) put_shear(ly - 1, pi);
+      else put_row(ly - 1, n, jx, jy);
       if (kTop && out_lane) top_sum = (double)n[2] - (double)a.t_top;
     }
   }
@@ -840,10 +872,12 @@ __global__ __launch_bounds__(64, kMomWaves<typename St::C>) void lb_moment_kerne
 }
 
 // M(0): the moments of the equilibrium start populations f(0) as the
-// population path stores them (solid nodes hold the wetting densities).
+// population path stores them (solid nodes hold the wetting densities), and the
+// xy moments of f_A(0) and f_B(0) into the two planes `shear`.
 template <class St>
 __global__ __launch_bounds__(256) void lb_moment_init(
-    typename St::C* __restrict__ dst, const double* __restrict__ rho_a,
+    typename St::C* __restrict__ dst, typename St::C* __restrict__ shear,
+    const double* __restrict__ rho_a,
     const double* __restrict__ rho_b, const double* __restrict__ temp,
     const double* __restrict__ ux0, const double* __restrict__ uy0,
     const uint8_t* __restrict__ solid, int lx, int pitch, long long pop_stride,
@@ -856,11 +890,12 @@ __global__ __launch_bounds__(256) void lb_moment_init(
   if (x >= lx) return;
   const size_t q = (size_t)y * lx + x, ps = (size_t)pop_stride;
   C* m = dst + (size_t)y * pitch + x;
+  C* xy = shear + (size_t)y * pitch + x;
   const C ref[3] = {St::kDev ? ref_a : C(0), St::kDev ? ref_b : C(0), St::kDev ? ref_t : C(0)};
   if (solid[q] != 0) {
     m[0] = rho_wall0 - ref[0];
     m[ps] = rho_wall1 - ref[1];
-    m[2 * ps] = m[3 * ps] = m[4 * ps] = C(0);
+    m[2 * ps] = m[3 * ps] = m[4 * ps] = xy[0] = xy[ps] = C(0);
     return;
   }
   const C ux = ux0 ? (C)ux0[q] : C(0), uy = uy0 ? (C)uy0[q] : C(0);
@@ -889,6 +924,8 @@ __global__ __launch_bounds__(256) void lb_moment_init(
   m[2 * ps] = momentum_x(f[0], f[1]);
   m[3 * ps] = momentum_y(f[0], f[1]);
   m[4 * ps] = sum9(f[2]);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) xy[k * ps] = (f[k][5] + f[k][7]) - (f[k][6] + f[k][8]);
 }
 
 }  // namespace tlbk

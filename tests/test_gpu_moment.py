@@ -213,3 +213,25 @@ def test_calls_that_read_the_previous_level(precision, name, n):
     for s in sims:
         s.step(n + 1)
     compare("stepped on")
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev"])
+@pytest.mark.parametrize("lx,ly", [(1, 1), (2, 5), (5, 3), (64, 1), (7, 2), (59, 4), (116, 30), (117, 7)])
+def test_stress_on_edge_shapes(precision, lx, ly):
+    """Stress and row averages, formed from moments, at the widths where a
+    wavefront's columns end and with one to a few rows; t = 0 with a velocity
+    start included. Bars as in the test above."""
+    case = droplet_case(lx, ly, seed=lx + ly)
+    rng = np.random.default_rng(lx)
+    u = rng.uniform(-0.02, 0.02, (2, ly, lx))
+    bar = 1e-13 if precision == "fp64" else 1e-6
+    print(precision, lx, ly, flush=True)
+    sims = [Simulation(dict(case["params"], u_wall=U_WALL), case["rho_a"], case["rho_b"], case["temp"], ux0=u[0],
+                       uy0=u[1], t_bottom=case["t_bottom"], precision=precision, launch={"fused": f})
+            for f in ("auto", "always")]
+    for n in (0, 1, 3, 2):
+        for s in sims:
+            s.step(n)
+        got, ref = (dict(s.stress(), **s.row_averages()) for s in sims)
+        for k in ref:
+            assert np.abs(got[k] - ref[k]).max() <= bar, (n, k)
