@@ -11,6 +11,8 @@
 // the two, where blocks are often recycled pages, the threads only compete
 // with the program's own: a run with its snapshot, ring / runtime, 17 MiB 2.7 /
 // 1.9 ms, 33 MiB 4.0 / 3.4, 49 MiB 4.0 / 4.7; without threads 2 to 4% slower.
+// Where there is no page-locked memory (or no host memory for the lists), the
+// runtime copies block by block, whatever the size.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -39,7 +41,7 @@ class Readout {
   // Page-locked memory of at least 64 KiB that a kernel may write, for results
   // read after the stream is waited for and before the next use of this
   // object; null when there is none.
-  void* page() { return reserve(kPage) == hipSuccess ? ring_ : nullptr; }
+  void* page() { return reserve(kPage); }
 
   // `parts` blocks of `bytes` bytes, one after the other in device memory, to
   // dst[0 .. parts - 1] (those that are not null), after the work on `stream`;
@@ -49,11 +51,12 @@ class Readout {
       int e = k;
       while (e < parts && dst[e]) ++e;
       if (e > k) {
+        const char* from = static_cast<const char*>(src) + k * bytes;
         hipError_t err;
         try {
-          err = run(static_cast<const char*>(src) + k * bytes, bytes, e - k, dst + k, stream);
+          err = run(from, bytes, e - k, dst + k, stream);
         } catch (const std::exception&) {  // no host memory for the lists; nothing was begun
-          err = hipErrorOutOfMemory;
+          err = each(from, bytes, e - k, dst + k, stream);
         }
         if (err != hipSuccess) return err;
       }
@@ -92,13 +95,27 @@ class Readout {
     std::memcpy(p.dst + m1, ring, p.len - m1);
   }
 
-  hipError_t reserve(size_t need) {
-    if (need <= size_) return hipSuccess;
-    if (ring_) (void)hipHostFree(ring_);
-    ring_ = nullptr;
-    size_ = 0;
-    const hipError_t e = hipHostMalloc(&ring_, need, hipHostMallocDefault);
-    if (e == hipSuccess) size_ = need;
+  // The ring of at least `need` bytes, or null.
+  char* reserve(size_t need) {
+    if (need > size_) {
+      if (ring_) (void)hipHostFree(ring_);
+      ring_ = nullptr;
+      size_ = 0;
+      if (hipHostMalloc(&ring_, need, hipHostMallocDefault) == hipSuccess) {
+        size_ = need;
+      } else {
+        (void)hipGetLastError();
+        ring_ = nullptr;
+      }
+    }
+    return static_cast<char*>(ring_);
+  }
+
+  // By the runtime's own copy.
+  static hipError_t each(const char* src, size_t bytes, int parts, void* const* dst, hipStream_t stream) {
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < parts && e == hipSuccess; ++k)
+      e = hipMemcpyAsync(dst[k], src + k * bytes, bytes, hipMemcpyDeviceToHost, stream);
     return e;
   }
 
@@ -106,15 +123,11 @@ class Readout {
     const size_t total = bytes * parts;
     if (total == 0) return hipSuccess;
     hipError_t e = hipSuccess;
-    if (total > kOneCopy && total < kThreaded && bytes < kFresh) {
-      for (int k = 0; k < parts && e == hipSuccess; ++k)
-        e = hipMemcpyAsync(dst[k], src + k * bytes, bytes, hipMemcpyDeviceToHost, stream);
-      return e;
-    }
+    if (total > kOneCopy && total < kThreaded && bytes < kFresh)
+      return each(src, bytes, parts, dst, stream);
     const size_t n = (total + kChunk - 1) / kChunk;
-    e = reserve(total <= kOneCopy ? std::max(total, kPage) : kSlots * kChunk);
-    if (e != hipSuccess) return e;
-    char* ring = static_cast<char*>(ring_);
+    char* ring = reserve(total <= kOneCopy ? std::max(total, kPage) : kSlots * kChunk);
+    if (!ring) return each(src, bytes, parts, dst, stream);
     if (total <= kOneCopy) {
       e = hipMemcpyAsync(ring, src, total, hipMemcpyDeviceToHost, stream);
       if (e == hipSuccess) e = hipStreamSynchronize(stream);

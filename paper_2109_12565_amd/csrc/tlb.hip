@@ -61,7 +61,7 @@ struct tlb_handle {
   uint16_t* link = nullptr;
   uint8_t* solid = nullptr;
   void* t_bottom = nullptr;        // C-typed copy of the bottom temperature
-  double* partials = nullptr;
+  double* partials = nullptr;      // [blocks + 1][kObsSums], the last for observables
   double* fields = nullptr;        // [7][ly][lx], allocated on first use
   double* rows = nullptr;          // [2][ly] row averages, allocated on first use
   // droplet detection, allocated on first use
@@ -729,7 +729,7 @@ Workspace workspace_layout(const tlb_params& p, size_t state_b, size_t nblocks,
   Workspace w;
   w.buf = 0;
   w.partials = 2 * up(state_b);
-  w.t_bottom = w.partials + up(nblocks * tlbk::kObsSums * sizeof(double));
+  w.t_bottom = w.partials + up((nblocks + 1) * tlbk::kObsSums * sizeof(double));
   w.solid = w.t_bottom + up((size_t)p.lx * sizeof(double));
   w.link = w.solid + up(n);
   w.tiles = w.link + up(n * sizeof(uint16_t));
@@ -882,7 +882,7 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
   } else {
     INIT_HIP(hipMalloc(&h->buf[0], buf_bytes));
     INIT_HIP(hipMalloc(&h->buf[1], buf_bytes));
-    INIT_HIP(hipMalloc(&h->partials, nblocks * tlbk::kObsSums * sizeof(double)));
+    INIT_HIP(hipMalloc(&h->partials, (nblocks + 1) * tlbk::kObsSums * sizeof(double)));
     INIT_HIP(hipMalloc(&h->t_bottom, lx * (is_fp64(h) ? sizeof(double) : sizeof(float))));
     INIT_HIP(hipMalloc(&h->solid, n));
     if (h->has_solid) INIT_HIP(hipMalloc(&h->link, n * sizeof(uint16_t)));
@@ -1042,12 +1042,18 @@ int tlb_observables(tlb_handle* h, tlb_obs* out) {
   oa.dtdy_sum = h->dtdy_sum;
   // the kernel writes its six values to the host's memory itself: a copy of
   // them costs as much as the kernel (step and observables at 128 x 64: 37 us,
-  // 28 without)
+  // 28 without),
+  // where there is page-locked memory
+  double copy[6];
   const double* v = static_cast<const double*>(h->readout.page());
-  if (!v) return fail(h, TLB_ENOMEM, "tlb_observables: no page-locked memory");
-  oa.out = const_cast<double*>(v);
+  oa.out = v ? const_cast<double*>(v)
+             : h->partials + partial_blocks(h->launch) * tlbk::kObsSums;
   hipLaunchKernelGGL(tlbk::lb_reduce_observables, dim3(1), dim3(256), 0, h->stream, oa);
   TLB_HIP(h, hipGetLastError());
+  if (!v) {
+    TLB_HIP(h, hipMemcpyAsync(copy, oa.out, sizeof copy, hipMemcpyDeviceToHost, h->stream));
+    v = copy;
+  }
   TLB_HIP(h, hipStreamSynchronize(h->stream));
   out->step = h->t;
   out->mass_a = v[0];
