@@ -35,13 +35,21 @@ class Readout {
   ~Readout() {
     for (hipEvent_t e : landed_)
       if (e) (void)hipEventDestroy(e);
+    if (page_) (void)hipHostFree(page_);
     if (ring_) (void)hipHostFree(ring_);
   }
 
-  // Page-locked memory of at least 64 KiB that a kernel may write, for results
-  // read after the stream is waited for and before the next use of this
-  // object; null when there is none.
-  void* page() { return reserve(kPage); }
+  // 64 KiB of page-locked memory that a kernel may write, for results read
+  // after the stream is waited for and before the next use of this object; null
+  // when there is none. Allocated at the first call (10 us or more: tlb_init
+  // makes it).
+  void* page() {
+    if (!page_ && hipHostMalloc(&page_, kPage, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      page_ = nullptr;
+    }
+    return page_;
+  }
 
   // `parts` blocks of `bytes` bytes, one after the other in device memory, to
   // dst[0 .. parts - 1] (those that are not null), after the work on `stream`;
@@ -95,8 +103,10 @@ class Readout {
     std::memcpy(p.dst + m1, ring, p.len - m1);
   }
 
-  // The ring of at least `need` bytes, or null.
+  // The ring of at least `need` bytes, or null: kOneCopy at first, so that it
+  // grows once at most.
   char* reserve(size_t need) {
+    need = std::max(need, kOneCopy);
     if (need > size_) {
       if (ring_) (void)hipHostFree(ring_);
       ring_ = nullptr;
@@ -123,10 +133,14 @@ class Readout {
     const size_t total = bytes * parts;
     if (total == 0) return hipSuccess;
     hipError_t e = hipSuccess;
-    if (total > kOneCopy && total < kThreaded && bytes < kFresh)
+    // (one block gains nothing that would pay for page-locked memory)
+    if (total <= kOneCopy ? total > kPage && total > size_ && parts == 1
+                          : total < kThreaded && bytes < kFresh)
       return each(src, bytes, parts, dst, stream);
     const size_t n = (total + kChunk - 1) / kChunk;
-    char* ring = reserve(total <= kOneCopy ? std::max(total, kPage) : kSlots * kChunk);
+    char* ring = total <= kPage      ? static_cast<char*>(page())
+                 : total <= kOneCopy ? reserve(total)
+                                     : reserve(kSlots * kChunk);
     if (!ring) return each(src, bytes, parts, dst, stream);
     if (total <= kOneCopy) {
       e = hipMemcpyAsync(ring, src, total, hipMemcpyDeviceToHost, stream);
@@ -221,8 +235,9 @@ class Readout {
     return sched_getaffinity(0, sizeof set, &set) == 0 ? std::max(1, CPU_COUNT(&set)) : 1;
   }
 
+  void* page_ = nullptr;
   void* ring_ = nullptr;
-  size_t size_ = 0;
+  size_t size_ = 0;  // of the ring
   hipEvent_t landed_[kSlots] = {};
 };
 

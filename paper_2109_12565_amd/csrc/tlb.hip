@@ -929,6 +929,7 @@ int init_impl(tlb_handle** out, const tlb_params* p, const double* rho_a, const 
   }
   INIT_HIP(hipStreamSynchronize(h->stream));
 #undef INIT_HIP
+  (void)h->readout.page();  // now, not in the first call that reads
   h->cur = 0;
   h->t = 0;
   *out = h;

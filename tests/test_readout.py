@@ -116,3 +116,17 @@ def test_blocks_arrive_with_and_without_page_locked_memory(reader, nbytes, parts
         c[0] = 0                # and once there is some again
         assert lib.page(r) and fetch(lib, r, nbytes, parts) == 0
 
+
+def test_small_read_outs_allocate_once(reader):
+    """Whatever the order, one page and one ring, which grows once for large
+    blocks; a single small block takes neither."""
+    lib, r, c = reader
+    assert lib.page(r) and c[2] == 1
+    assert fetch(lib, r, 512 * 1024, 1) == 0 and c[2] == 1
+    for nbytes, parts in ((64, 5), (512, 2), (65536, 2), (2 * MIB // 5, 5), (100000, 5), (65536, 5), (512 * 1024, 1)):
+        assert fetch(lib, r, nbytes, parts) == 0
+    assert c[2] == 2 and c[1] == 2
+    for _ in range(2):
+        assert fetch(lib, r, 33 * MIB, 2) == 0
+        assert fetch(lib, r, 100000, 5) == 0
+    assert c[2] == 3 and c[1] == 2
