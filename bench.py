@@ -29,26 +29,21 @@ import workloads  # noqa: E402
 METRIC = "MLUPS and % HBM roofline (FP32 vs FP16-storage); adjoint/forward time ratio"
 HBM_PEAK_GBS = 8000.0
 ANALYSIS_CALLS = 5   # steady-state calls of the row averages and the droplet analysis
-# Algorithmic bytes per node update: the state read once and written once,
-# plus one byte of solid flag when the lattice has solid cells. FP64, FP32 and
-# FP16 storage keep, at tau = tau_g = 1, the five moments of the pulled
-# populations (FP16: in FP32, of populations rounded to 16 bits); else
-# the 27 populations (FP16 / BF16 deviations: 24 16-bit moving populations and
-# 3 FP32 rest populations).
+# Algorithmic bytes per node update: the state read once and written once.
+# Handles that advance moments (launch_info's moment_rows) keep the five moments
+# of the pulled populations (FP16: in FP32, of populations rounded to 16 bits)
+# and read link masks in the tiles that hold solid links only, which is not
+# counted; else the 27 populations (FP16 / BF16 deviations: 24 16-bit moving
+# populations and 3 FP32 rest populations), plus one byte of solid flag when the
+# lattice has solid cells.
 BYTES_PER_UPDATE = {"fp64": 432, "fp32": 216, "fp16dev": 120, "bf16dev": 120, "fix16dev": 108}
 MOMENT_BYTES_PER_UPDATE = {"fp64": 80, "fp32": 40, "fp16dev": 40}
 KERNEL_SOURCES = ("paper_2109_12565_amd/csrc/lb_kernels.hpp",
                   "paper_2109_12565_amd/csrc/lb_moment.hpp",
+                  "paper_2109_12565_amd/csrc/moment_tiles.hpp",
                   "paper_2109_12565_amd/csrc/lb_step2.hpp",
                   "paper_2109_12565_amd/csrc/launch_impl.hpp",
                   "paper_2109_12565_amd/csrc/tlb.hip")
-
-
-def keeps_moments(w: dict, precision: str) -> bool:
-    """The library's choice of state for a workload (fused left at its default)."""
-    return (precision in MOMENT_BYTES_PER_UPDATE and w["params"]["tau"] == 1.0
-            and w["params"]["tau_g"] == 1.0
-            and 27 * w["lx"] * w["ly"] * {"fp64": 8, "fp32": 4, "fp16dev": 2}[precision] < 0.8 * 2**32)
 
 
 def kernel_hash() -> str:
@@ -211,7 +206,7 @@ def precision_study(steps: int, every: int, storages) -> dict:
         e["mass_a_drift"] = (obs["mass_a"] - m0[pr]["mass_a"]) / m0[pr]["mass_a"]
         e["mass_b_drift"] = (obs["mass_b"] - m0[pr]["mass_b"]) / m0[pr]["mass_b"]
         info = sim.launch_info()
-        e["launch"] = ("moment steps" if keeps_moments(w, pr) else
+        e["launch"] = ("moment steps" if info["moment_rows"] > 0 else
                        "fused two-step, %d lanes, %d-row chunks" % (info["fused_lanes"], info["fused_rows"])
                        if info["fused_rows"] > 0 else "single steps")
         out["storages"][pr] = e
@@ -246,7 +241,8 @@ def companion_runs(config: str, precision: str) -> dict:
             launch = sim.launch_info()
         return {"workload": w["name"], "storage": prec, "steps": steps,
                 "mlups": round(w["lx"] * w["ly"] * steps / (ms * 1e-3) / 1e6, 1),
-                "ms_per_step": round(ms / steps, 4), "fused": launch["fused_rows"] > 0 and not keeps_moments(w, prec)}
+                "ms_per_step": round(ms / steps, 4), "moments": launch["moment_rows"] > 0,
+                "fused": launch["fused_rows"] > 0 and launch["moment_rows"] == 0}
 
     other = "fp16dev" if precision != "fp16dev" else "fp32"
     return {"other_storage": run(config, other, 300, 20),
@@ -344,8 +340,8 @@ def main() -> int:
         return best, out
 
     # stress fields + row averages of the same time level (Couette rheology
-    # observables): one pass of the step kernel without store, then the row
-    # reduction and the copy of 2 * ly doubles (synchronising)
+    # observables): passes of the step kernel, then the row reduction and the
+    # copy of 2 * ly doubles (synchronising)
     t_rows, rows = best_of(sim.row_averages)
     # droplet detection of the same time level: fields pass, labelling,
     # exact per-droplet sums, droplet Nusselt numbers, copy of the results
@@ -359,7 +355,7 @@ def main() -> int:
     # without the fused kernel they differ by that many single steps (of the
     # populations or the moments).
     launch = sim.launch_info()
-    moments = keeps_moments(w, args.precision)
+    moments = launch["moment_rows"] > 0
     fused = launch["fused_rows"] > 0 and not moments
 
     def call_ms(n, reps=3):
@@ -391,8 +387,8 @@ def main() -> int:
     n_single = args.steps - 2 * n_fused
     nodes = w["lx"] * w["ly"]
     mlups = nodes * args.steps / (total_ms * 1e-3) / 1e6
-    bpn = ((MOMENT_BYTES_PER_UPDATE if moments else BYTES_PER_UPDATE)[args.precision]
-           + (1 if w["solid"] is not None else 0))
+    bpn = (MOMENT_BYTES_PER_UPDATE[args.precision] if moments else
+           BYTES_PER_UPDATE[args.precision] + (1 if w["solid"] is not None else 0))
     kernel, updates = (("lb_step2_kernel", 2) if n_fused > 0 else
                        ("lb_moment_kernel" if moments else "lb_step_kernel", 1))
     if fused and n_fused == 0:  # fused kernel chosen, but too few steps to use it

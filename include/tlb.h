@@ -333,8 +333,8 @@ int64_t tlb_time(const tlb_handle *h);
  * the fused two-step kernel applies (tau = tau_g = 1, flat walls at rest or
  * moving; blocks of fused_lanes lanes, strips of fused_strip stored columns,
  * chunks of fused_rows rows): tlb_step advances pairs of steps with it, ending
- * each call with a single step, unless the handle advances moments (with
- * TLB_FUSED_AUTO, see tlb_step). Host struct, written by the
+ * each call with a single step, unless the handle advances moments (see
+ * tlb_moment_info). Host struct, written by the
  * call. Returns TLB_EINVAL on a NULL argument. */
 typedef struct tlb_launch {
   int32_t bx, rows, grid_x, grid_y;
@@ -342,6 +342,18 @@ typedef struct tlb_launch {
   int32_t fused_lanes;
 } tlb_launch;
 int tlb_launch_info(const tlb_handle *h, tlb_launch *out);
+
+/* Geometry of the moment steps (see tlb_step): one wavefront per chunk of
+ * `rows` rows of a strip of `strip` stored columns, grid_x strips x grid_y
+ * chunks; with solid cells the steps run `tiles` tiles in place of the chunks,
+ * `linked` of which hold solid links. rows = 0: the handle advances
+ * populations, as tlb_launch_info tells. Host struct, written by the call.
+ * Returns TLB_EINVAL on a NULL argument. */
+typedef struct tlb_moment_launch {
+  int32_t rows, strip, grid_x, grid_y;
+  int32_t tiles, linked;
+} tlb_moment_launch;
+int tlb_moment_info(const tlb_handle *h, tlb_moment_launch *out);
 
 /* Free the handle and its device memory. NULL is accepted. */
 int tlb_destroy(tlb_handle *h);

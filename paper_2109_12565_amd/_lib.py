@@ -24,8 +24,8 @@ EXPORTS = (
     "tlb_init", "tlb_init_external", "tlb_workspace_bytes", "tlb_step", "tlb_observables",
     "tlb_get_fields", "tlb_get_stress",
     "tlb_row_averages", "tlb_droplets", "tlb_droplets_noalloc", "tlb_get_populations",
-    "tlb_set_bottom_temperature", "tlb_forward_taped", "tlb_adjoint_step", "tlb_time", "tlb_launch_info", "tlb_destroy",
-    "tlb_last_error",
+    "tlb_set_bottom_temperature", "tlb_forward_taped", "tlb_adjoint_step", "tlb_time", "tlb_launch_info",
+    "tlb_moment_info", "tlb_destroy", "tlb_last_error",
 )
 
 
@@ -67,6 +67,10 @@ class Launch(ctypes.Structure):
     _fields_ = [(k, ctypes.c_int32) for k in
                 ("bx", "rows", "grid_x", "grid_y",
                  "fused_rows", "fused_strip", "fused_grid_x", "fused_grid_y", "fused_lanes")]
+
+
+class MomentLaunch(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_int32) for k in ("rows", "strip", "grid_x", "grid_y", "tiles", "linked")]
 
 
 class Droplet(ctypes.Structure):
@@ -119,6 +123,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.tlb_time.argtypes = [vp]
     lib.tlb_time.restype = ctypes.c_int64
     lib.tlb_launch_info.argtypes = [vp, ctypes.POINTER(Launch)]
+    lib.tlb_moment_info.argtypes = [vp, ctypes.POINTER(MomentLaunch)]
     lib.tlb_destroy.argtypes = [vp]
     lib.tlb_last_error.argtypes = [vp]
     lib.tlb_last_error.restype = ctypes.c_char_p
@@ -126,7 +131,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                  "tlb_get_fields", "tlb_get_stress",
                  "tlb_row_averages", "tlb_droplets", "tlb_droplets_noalloc",
                  "tlb_get_populations", "tlb_set_bottom_temperature",
-                 "tlb_forward_taped", "tlb_adjoint_step", "tlb_launch_info", "tlb_destroy"):
+                 "tlb_forward_taped", "tlb_adjoint_step", "tlb_launch_info", "tlb_moment_info",
+                 "tlb_destroy"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
@@ -264,11 +270,14 @@ class Simulation:
         return int(self._lib.tlb_time(self._h))
 
     def launch_info(self) -> dict:
-        """Launch geometry of the step kernels (fused_rows > 0: the fused
-        two-step kernel advances pairs of steps)."""
-        g = Launch()
+        """Launch geometry of the step kernels. moment_rows > 0: steps advance the
+        moments; else fused_rows > 0: the fused two-step kernel advances pairs
+        of steps."""
+        g, m = Launch(), MomentLaunch()
         self._check(self._lib.tlb_launch_info(self._h, ctypes.byref(g)))
-        return {k: getattr(g, k) for k, _ in Launch._fields_}
+        self._check(self._lib.tlb_moment_info(self._h, ctypes.byref(m)))
+        return dict({k: getattr(g, k) for k, _ in Launch._fields_},
+                    **{"moment_" + k: getattr(m, k) for k, _ in MomentLaunch._fields_})
 
     def step(self, n: int = 1) -> "Simulation":
         self._check(self._lib.tlb_step(self._h, int(n)))

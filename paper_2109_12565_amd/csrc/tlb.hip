@@ -1020,6 +1020,20 @@ int tlb_launch_info(const tlb_handle* h, tlb_launch* out) {
   return TLB_OK;
 }
 
+int tlb_moment_info(const tlb_handle* h, tlb_moment_launch* out) {
+  if (!h || !out) return TLB_EINVAL;
+  *out = tlb_moment_launch{};
+  if (!has_moments(h)) return TLB_OK;
+  const tlbh::Geometry& g = h->launch;
+  out->rows = g.rows_m;
+  out->strip = g.strip_m;
+  out->grid_x = (int32_t)g.grid_m.x;
+  out->grid_y = (int32_t)g.grid_m.y;
+  out->tiles = h->ntiles;
+  out->linked = h->nlinked;
+  return TLB_OK;
+}
+
 int tlb_observables(tlb_handle* h, tlb_obs* out) {
   if (!h || !out) return fail(h, TLB_EINVAL, "tlb_observables: NULL argument");
   // the last population step of tlb_step left the sums of the current time;

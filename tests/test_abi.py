@@ -186,3 +186,18 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode == 2
     line = r.stdout.strip().splitlines()[-1]
     assert "one GPU only" in line and '"n_gpus": 2' in line
+
+
+def test_moment_info_layout_and_null_arguments(tmp_path):
+    """The moment geometry's struct as the C compiler lays it out, and NULL."""
+    names = [k for k, _ in tlb.MomentLaunch._fields_]
+    src = tmp_path / "m.c"
+    src.write_text('#include <stdio.h>\n#include <stddef.h>\n#include "tlb.h"\nint main(void){'
+                   'printf("%zu", sizeof(tlb_moment_launch));'
+                   + "".join(f'printf(" %zu", offsetof(tlb_moment_launch, {k}));' for k in names) + "return 0;}\n")
+    subprocess.run(["gcc", "-I", os.path.dirname(HEADER), str(src), "-o", str(tmp_path / "m")], check=True)
+    out = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True, check=True).stdout.split()
+    assert [int(v) for v in out] == [ctypes.sizeof(tlb.MomentLaunch)] + [
+        getattr(tlb.MomentLaunch, k).offset for k in names]
+    lib = tlb.load_library()
+    assert lib.tlb_moment_info(None, ctypes.byref(tlb.MomentLaunch())) == tlb.TLB_EINVAL

@@ -235,3 +235,29 @@ def test_stress_on_edge_shapes(precision, lx, ly):
         got, ref = (dict(s.stress(), **s.row_averages()) for s in sims)
         for k in ref:
             assert np.abs(got[k] - ref[k]).max() <= bar, (n, k)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev", "bf16dev", "fix16dev"])
+def test_launch_info_tells_what_the_steps_advance(precision):
+    case = CASES["small"]()
+    print(precision, flush=True)
+    info = make(case, precision).launch_info()
+    assert (info["moment_rows"] > 0) == (precision in ("fp64", "fp32", "fp16dev"))
+    if info["moment_rows"]:
+        ly, lx = case["rho_a"].shape
+        assert info["moment_strip"] <= 58 and info["moment_strip"] * info["moment_grid_x"] >= lx
+        assert info["moment_rows"] * info["moment_grid_y"] >= ly and info["moment_tiles"] == 0
+    for fused in ("never", "always"):
+        assert make(case, precision, fused).launch_info()["moment_rows"] == 0
+    assert make(case, precision, tau=1.2).launch_info()["moment_rows"] == 0
+    posts = make(CASES["posts"](), precision).launch_info()
+    assert (posts["moment_tiles"] > posts["moment_linked"] > 0) == (posts["moment_rows"] > 0)
+
+
+def test_launch_info_near_the_4_gib_limit():
+    """3.6 and 4.1 GiB of populations on either side of the limit."""
+    for ly, moments in ((4400, True), (5000, False)):
+        a = np.full((ly, 4096), 0.7)
+        print("fp64 4096 x", ly, flush=True)
+        with Simulation(dict(CASES["small"]()["params"]), a, a, a, t_bottom=np.ones(4096), precision="fp64") as sim:
+            assert (sim.launch_info()["moment_rows"] > 0) == moments
