@@ -218,9 +218,9 @@ void launch_moment(const Device& d, MomentPass pass, const void* src, void* dst)
   a.ntiles = d.ntiles;
   a.nlinked = d.nlinked;
   a.src_full = d.src_full;
-  // (the fused kernel without solid cells loads T_w, and with it 2 w T_w, in a
-  // block of its own at both levels, the others at the second)
-  a.round_wall = d.pair_second || (d.pair_first && !d.has_solid && !St::kDev);
+  // (the fused kernel without solid cells, at rest, loads T_w, and with it 2 w
+  // T_w, in a block of its own at both levels, the others at the second)
+  a.round_wall = d.pair_second || (d.pair_first && !d.has_solid && !d.moving && !St::kDev);
   a.out = static_cast<double*>(dst);
   const tlb_params& p = *d.p;
   // combined from the constants as the population kernels round them, so

@@ -638,13 +638,23 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
         }
         if constexpr ((kMode & kModeMoving) != 0 && !kG) {
           // moving flat walls (Sec. 2.2): the bounced diagonal links gain
-          // +- 6 w_5 rho u_w
-          if (!kIn && q == 0) {
-            const C m = C(6) * w_dir<C>(5) * a.uw0;
-            u5 = fma(m, dens[k], u5);
-            u6 = fma(-m, dens[k], u6);
+          // +- 6 w_5 rho u_w, rho the sum of the node's populations (between
+          // the levels of a fused launch the moment itself)
+          if (!kIn && (q == 0 || q == ly - 1)) {
+            C rw = dens[k];
+            if constexpr (kSame && !kSplit) {
+              rw = f[0];
+#pragma unroll
+              for (int i = 1; i < 9; ++i) rw += f[i];
+              if constexpr (kDev) rw += ref[k];
+            }
+            if (q == 0) {
+              const C m = C(6) * w_dir<C>(5) * a.uw0;
+              u5 = fma(m, rw, u5);
+              u6 = fma(-m, rw, u6);
+            }
+            if (q == ly - 1) top_rho[k] = rw;
           }
-          if (!kIn && q == ly - 1) top_rho[k] = dens[k];
         }
         cp[k] = (f[0] + l1) + (u2 + l3);
         c5[k] = u5;

@@ -261,3 +261,16 @@ def test_launch_info_near_the_4_gib_limit():
         print("fp64 4096 x", ly, flush=True)
         with Simulation(dict(CASES["small"]()["params"]), a, a, a, t_bottom=np.ones(4096), precision="fp64") as sim:
             assert (sim.launch_info()["moment_rows"] > 0) == moments
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16dev"])
+@pytest.mark.parametrize("name", ["small", "posts", "narrow"])
+def test_moving_walls_are_the_fused_launches_bit_for_bit(precision, name):
+    case = CASES[name]()
+    print(precision, name, flush=True)
+    a, b = (make(case, precision, f, u_wall=U_WALL) for f in ("auto", "always"))
+    for n in (0, 1, 2, 3, 4, 9, 60):
+        a.step(n)
+        b.step(n)
+        assert np.array_equal(a.populations(), b.populations()), (n, a.t)
+
