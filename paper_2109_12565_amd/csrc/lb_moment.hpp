@@ -128,10 +128,11 @@ __device__ inline typename St::C recip_moment(typename St::C v) {
 // 2^k - 1) with x = k ln 2 + f, |f| <= ln 2 / 2, so that small rho keeps its
 // relative precision (then k = 0). e^f - 1 = f + f^2 q(f), q the Taylor sum to
 // f^14 / 14! (4e-18). The library expm1 takes 53 instructions a value, this
-// 26, of a row's 370 in all. x is kept inside the range where 2^k is finite
-// and not zero.
+// 26, of a row's 370 in all. Below k = -1100, 2^k is zero and psi = rho0, at any
+// density. A clamp drops NaN, so it is k's copy for the exponent that is kept
+// in range, and f carries the NaN of a density into psi.
 __device__ inline double psi_moment(double rho, double rho0, double inv_rho0) {
-  const double x = fmin(fmax(-rho * inv_rho0, -700.0), 709.0);
+  const double x = -rho * inv_rho0;
   const double k = __builtin_rint(x * 1.44269504088896340736);
   double f = fma(k, -0.693147180559945286, x);
   f = fma(k, -2.31904681384629956e-17, f);
@@ -148,7 +149,7 @@ __device__ inline double psi_moment(double rho, double rho0, double inv_rho0) {
   q = fma(f, q, 1.0 / 6.0);
   q = fma(f, q, 0.5);
   const double e = fma(f * f, q, f);
-  const double s = __builtin_ldexp(-rho0, (int)k);
+  const double s = __builtin_ldexp(-rho0, (int)fmax(k, -1100.0));
   return fma(s, e, s + rho0);
 }
 

@@ -14,6 +14,7 @@ import pytest
 import workloads
 from oracle.oracle import ModelParams, Oracle
 from paper_2109_12565_amd import Simulation
+from paper_2109_12565_amd._lib import TLB_ENUMERIC, TlbError
 
 from test_gpu_parity import field_errors, pop_errors, posts_case, rel
 from test_gpu_step2 import CASES, assert_close_state, droplet_case
@@ -310,3 +311,33 @@ def test_fp16_moment_run_against_the_oracle(name):
     f, r = sim.fields(), ora.fields()
     for k in ("rho_a", "rho_b", "temp"):
         assert np.abs(f[k] - r[k]).max() <= 2e-3 * np.abs(r[k]).max(), k
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev"])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_a_broken_density_spreads_as_in_population_steps(precision, bad):
+    """NaN reaches the same nodes, through forces and streaming alike, and the
+    observables report it. (FP64 forms a force's x part from differences that
+    pass over the node's own column, where a NaN above or below it stays, so
+    u_x is NaN at nodes whose u_y alone is NaN otherwise; their populations are
+    NaN either way.)"""
+    case = dict(posts_case())
+    ly, lx = case["rho_a"].shape
+    case["rho_a"] = case["rho_a"].copy()
+    case["rho_a"][ly // 2, lx // 2] = case["rho_a"][ly - 3, 0] = bad
+    print(precision, bad, flush=True)
+    sims = [make(case, precision, f) for f in ("auto", "never")]
+    for n in (0, 1, 2):
+        for s in sims:
+            s.step(n)
+        got, ref = (s.fields() for s in sims)
+        for k in ("rho_a", "rho_b", "temp"):
+            assert np.array_equal(np.isnan(got[k]), np.isnan(ref[k])), (n, k)
+        u, v = (np.isnan(f["ux"]) | np.isnan(f["uy"]) for f in (got, ref))
+        assert np.array_equal(u, v), n
+        got, ref = (np.isnan(s.populations()) for s in sims)
+        assert np.array_equal(got, ref)
+        for s in sims:
+            with pytest.raises(TlbError) as e:
+                s.observables()
+            assert e.value.code == TLB_ENUMERIC
