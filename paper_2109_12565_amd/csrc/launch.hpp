@@ -21,7 +21,7 @@ struct Geometry {
   int lanes2 = 256;  // lanes per block (kStep2Lanes or kStep2LanesNarrow)
   int strip2 = 0;    // stored columns per strip (lanes2 - kStep2Halo at most)
   dim3 grid2;
-  // moment state (tau = tau_g = 1, FP64 / FP32); rows_m == 0: not used
+  // moment state (tau = tau_g = 1, FP64 / FP32 / FP16); rows_m == 0: not used
   int rows_m = 0;    // rows per wavefront chunk
   int strip_m = 0;   // stored columns per wavefront
   dim3 grid_m;       // strips x chunks, one wavefront each
@@ -34,7 +34,7 @@ struct Geometry {
 constexpr int kStep2Lanes = 256;
 constexpr int kStep2LanesNarrow = 128;
 constexpr int kStep2Halo = 10;
-// Stored columns per wavefront of the moment kernel, at most.
+// Stored columns per wavefront of the moment kernel, at most (tlbk::kMomStrip).
 constexpr int kMomentStrip = 58;
 
 // Everything a launch needs from a handle.

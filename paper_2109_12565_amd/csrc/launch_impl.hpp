@@ -8,6 +8,8 @@
 
 namespace tlbh {
 
+static_assert(kMomentStrip == tlbk::kMomStrip, "columns of a moment wavefront");
+
 namespace detail {
 
 template <typename C>

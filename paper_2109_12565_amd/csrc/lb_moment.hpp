@@ -262,8 +262,7 @@ __device__ __forceinline__ void unroll(F&& f) {
   unroll_list(f, std::make_integer_sequence<int, N>{});
 }
 
-// Rows of the register rings: five in use, and so many more loads in flight.
-template <typename C>
+// Rows of the register rings: five in use, two of them with loads in flight.
 constexpr int kMomRing = 5;
 
 // The rows y0 .. y1 - 1 of one strip, by one wavefront. kModeSolid: link masks
@@ -307,14 +306,16 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   const PopMem<Store<C>, 0> msrc(a.src, (uint64_t)plane_b * 5);
   const uint32_t vcol = (uint32_t)xw * sizeof(C);
   // Lanes that store nothing get an offset beyond the five planes (which are
-  // below 5/27 of 4 GiB), where the buffer's range check drops the store:
-  // no branch around the stores.
+  // below 2 GiB, as tlb.hip asserts), where the buffer's range check drops the
+  // store: no branch around the stores.
   const PopMem<Store<C>, 0> mdst(a.dst, (uint64_t)plane_b * 5);
   const uint32_t vout = out_lane ? vcol : 0x80000000u;
 
   // Rings over rows, slot = iteration mod R (row r is slot S of its stage):
-  // five rows in use and kAhead rows of loads in flight.
-  constexpr int R = kMomRing<C>, kAhead = R - 3;
+  // the rows that the forces of row q = r - 2 need; the loads of rows r + 1 and
+  // r + kAhead are in flight in the slots of r - 4 and r - 3, whose moments are
+  // spent (psi and its differences have arrays of their own).
+  constexpr int R = kMomRing, kAhead = R - 3;
   C rho[R][2], mx[R], my[R], tt[R];   // loaded moments
   [[maybe_unused]] C raw[R][2];       // kDev: densities as loaded
   C psi[R][2], dpx[R][2], drx[R][2];  // psi and the x-differences of psi and rho

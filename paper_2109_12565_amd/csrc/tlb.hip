@@ -332,7 +332,15 @@ size_t moment_bytes(const tlb_handle* h) {
 
 bool has_moments(const tlb_handle* h) { return h->launch.rows_m > 0; }
 
-// Slot k of the moment state.
+// Slot k of the moment state: three of them in a population buffer, each below
+// the 2 GiB that the kernel's dropped stores rely on (handles with more than 4
+// GiB of populations advance those).
+constexpr bool moment_slots_fit(size_t csize, size_t buffer_bytes_per_node) {
+  return 3 * 5 * csize <= buffer_bytes_per_node &&
+         (size_t)0xFFFFFFFF / buffer_bytes_per_node * 5 * csize < ((size_t)1 << 31);
+}
+static_assert(moment_slots_fit(8, 27 * 8) && moment_slots_fit(4, 27 * 4) &&
+              moment_slots_fit(4, (27 + 3 * 2) * 2), "moment slots");
 void* moment_slot(const tlb_handle* h, int k) {
   return static_cast<char*>(h->buf[1]) + (size_t)k * moment_bytes(h);
 }
@@ -715,9 +723,9 @@ int check_params(const tlb_params* p) {
 }
 
 // Layout of the step path's device buffers (each part 256-byte aligned):
-// both population buffers, the per-block observable partials, the
-// observables, the bottom temperature, the solid flags, the link masks and
-// the tile list.
+// both population buffers, the per-block observable partials (and one set
+// more), the bottom temperature, the solid flags, the link masks and the tile
+// list.
 struct Workspace {
   size_t buf = 0, partials = 0, t_bottom = 0, solid = 0, link = 0, tiles = 0, total = 0;
 };
