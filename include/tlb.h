@@ -205,15 +205,18 @@ int tlb_init_external(tlb_handle **out, const tlb_params *p, const double *rho_a
  * steps, and pairs of calls of one, leave the state where it was in memory: a
  * HIP graph that captured them advances it at every replay (tlb_time does not
  * see replays). Results agree with single population
- * steps to rounding either way. Returns TLB_EINVAL for nsteps < 0 or a
+ * steps to rounding, except that FP16_DEV and BF16_DEV handles round to 16 bits
+ * once in a pair of steps, single population steps (TLB_FUSED_NEVER) every
+ * time. Returns TLB_EINVAL for nsteps < 0 or a
  * NULL handle, TLB_EDEVICE on a launch failure. */
 int tlb_step(tlb_handle *h, int64_t nsteps);
 
 /* Observables at the current time (synchronises the stream). After
  * population steps the sums are already on the device (formed by the last
  * one); otherwise (moment steps, a taped run, a new bottom temperature) the
- * time level is evaluated. Returns TLB_ENUMERIC if a component mass is not
- * finite. */
+ * time level is evaluated. The sums reach the host through 64 KiB of
+ * page-locked memory that tlb_init allocates, or a copy where there is none.
+ * Returns TLB_ENUMERIC if a component mass is not finite. */
 int tlb_observables(tlb_handle *h, tlb_obs *out);
 
 /* Fields at the current time into host arrays of ly*lx doubles (any may be

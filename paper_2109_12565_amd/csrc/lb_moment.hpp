@@ -28,15 +28,23 @@
 // LDS and no barrier, so nothing but the loads is waited for, and the
 // occupancy is set by the registers alone.
 //
-// Bound and measurements (4096 x 2048, flat walls, one step): FP32 127 us, 336
-// MB = 2.6 TB/s; 376 vector instructions a row of 64 columns (the two-step
-// kernel: 638 a node) of 4.4 to 4.9 cycles each on a SIMD, so the instruction
-// issue; a variant of 272 instructions that rounds differently (see
-// kSameRounding) takes 97. FP64 178 us, 671 MB = 3.8 TB/s. Before: 263 and 677
-// us a step (two-step kernel), 377 and 752 (single steps). Smaller lattices:
-// FP32 15.7 us at 1024 x 512 (25.3), 6.1 at 128 x 64 (12); FP64 17.8 (52.2) and
-// 6.4 (17). FP16 storage 130 us at 4096 x 2048 (247 in the two-step kernel), the
-// rounding adding a tenth to the FP32 instructions.
+// Bound and measurements (4096 x 2048, posts along the bottom wall, average of
+// a run): FP32 119 to 127 us a step on different boards (a pair's first step
+// 122, its second 132 under the profiler), 336 MB = 2.6 to 2.8 TB/s; 376 vector
+// instructions a row of 64 columns (the two-step kernel: 638 a node) of 4.4 to
+// 4.9 cycles each on a SIMD, so the instruction issue; a variant of 272
+// instructions that rounds differently (see kSameRounding) takes 97. FP64 176
+// us, 671 MB = 3.8 TB/s. FP16 storage 124 to 130, the rounding adding a tenth to
+// the FP32 instructions. Two-step kernel: 266, 668 and 248 us a step; single
+// steps in FP32 and FP64 377 and 752. Smaller lattices: FP32 14.6 us at 1024 x
+// 512 (25.3 in the two-step kernel), 6.0 at 128 x 64 (12); FP64 17.0 at 1000 x
+// 500 (47.6) and 6.0 at 128 x 64 (16.4).
+//
+// FP64 results differ in rounding from population steps: 1 / rho from the
+// hardware's reciprocal and two Newton steps (1 ulp), psi from a series of its
+// own, sums in another order. Both stay at rounding level from a 64-bit
+// reference (after 100 to 200 steps 4.9e-15 / 6.0e-15 population / moment steps
+// in a gradient, 7.2e-14 / 7.7e-14 in a sheared flow).
 #pragma once
 
 #include <utility>
@@ -186,14 +194,16 @@ __device__ inline void equilibria(double rho, double tx, double ty, double (&f)[
 }
 
 // FP32 evaluates every value of a step with the operations of the population
-// kernels, one by one, multiply-adds fused as in them: a run gives bit for bit
-// the state of the launches it replaces, and a chaotic flow (coalescing
-// droplets amplify a rounding a thousandfold within 300 steps) the same
-// events. FP64 has no such need at 1e-13 and takes the shorter forms above.
+// kernels, one by one, multiply-adds fused as in them, walls at rest or moving:
+// a run gives bit for bit the state of the launches it replaces, and a chaotic
+// flow (coalescing droplets amplify a rounding a thousandfold within 300 steps)
+// the same events. FP64 has no such need at 1e-13 and takes the shorter forms
+// above.
 template <typename C> constexpr bool kSameRounding = sizeof(C) == 4;
 
-// The FP16 deviation storage keeps its moments in FP32: what its populations, rounded to 16 bits where a launch of the population kernels
-// would have stored them, add up to. They are rounded in registers, after
+// The FP16 deviation storage keeps its moments in FP32: what its populations,
+// rounded to 16 bits where a launch of the population kernels would have stored
+// them, add up to. They are rounded in registers, after
 // every step but the first of a pair (kMomSplit: the second one's start), so a
 // run gives the results of 16-bit populations while 40 bytes a node move
 // instead of 120. Moments of rounded populations are deviations from the
@@ -845,11 +855,16 @@ __device__ __forceinline__ void moment_rows(const MomentArgs<typename St::C>& ma
   }
 }
 
-// Wavefronts per SIMD the registers are limited for. FP32 takes about 160
-// VGPRs; held to the 128 of four wavefronts it spills (a body of 140 ran 17%
-// slower there). FP64, with twice the registers per value, spills a little at
-// the 256 of two wavefronts, and runs as fast as unspilled with one (171 us a
-// step of 4096 x 2048 either way).
+// Wavefronts per SIMD the registers are limited for. FP32 steps take 143 to 168
+// VGPRs; held to the 128 of four wavefronts they spill (a body of 140 ran 17%
+// slower there), and at the 168 of three only a pair's second step with solid
+// cells does (10, 31 with moving walls). Limited to two, nothing spills, and 4096
+// x 2048 takes 123 us a step (119), 174 with posts over the lower third (157).
+// FP16 spills more at three: 4 to 9 on flat walls, 84 to 108 with solid cells,
+// where two would be faster (lower third 180 us, 198 at three; posts along the
+// bottom only 125, 124; 333 x 129 8.6, 14.8). FP64, with twice the registers per
+// value, spills 14 to 62 at the 256 of two wavefronts, and runs as fast as
+// unspilled with one (171 us a step of 4096 x 2048 either way).
 template <typename C>
 constexpr int kMomWaves = sizeof(C) == 4 ? 3 : 2;
 

@@ -252,9 +252,10 @@ tlbh::Geometry choose_launch(const tlb_params& p, size_t buffer_bytes, bool soli
 
   // Moment state: the library's own choice at tau = tau_g = 1 in FP64, FP32 and
   // FP16 storage below 4 GiB (per step, moments / the launches it replaces:
-  // FP32 4096 x 2048 127 / 263 us, 1024 x 512 15.7 / 25.3, 128 x 64 6.1 / 12.0;
-  // FP64 178 / 677, 17.8 / 52.2, 6.4 / 17.0; FP16 4096 x 2048 130 / 247). Any
-  // explicit choice of the fused kernel keeps that one.
+  // FP32 4096 x 2048 119 / 266 us, 1024 x 512 14.6 / 25.3, 128 x 64 6.0 / 12.0;
+  // FP64 176 / 668, 128 x 64 6.0 / 16.4; FP16 4096 x 2048 124 / 248; lattices full
+  // of posts FP32 201 / 415, FP64 324 / 862, FP16 313 / 379). Any explicit choice
+  // of the fused kernel keeps that one.
   const bool moments = tau_one && !l.wide && p.fused == TLB_FUSED_AUTO && p.fused_rows == 0 &&
                        p.fused_strip == 0 && p.fused_lanes == 0 &&
                        (p.precision == TLB_FP64 || p.precision == TLB_FP32 ||
@@ -268,7 +269,9 @@ tlbh::Geometry choose_launch(const tlb_params& p, size_t buffer_bytes, bool soli
     // chunks for one / two / three wavefronts per SIMD: FP32 512 x 256 8.7 /
     // 9.5 / 10.3 us, 1024 x 512 16.1 / 15.0 / 16.8, 2048 x 512 24.2 / 23.1 /
     // 24.3, 4096 x 2048 147 / 128 / 122; FP64 512 x 256 9.7 / 11.2 / 13.4,
-    // 1024 x 512 17.8 / 18.5 / 22.6, 2048 x 1024 - / 47.1 / 53.1.
+    // 1024 x 512 17.8 / 18.5 / 22.6, 2048 x 1024 - / 47.1 / 53.1. In FP32 two
+    // is the best of the three in between and within 10% at both ends, where
+    // one and three would be better; a finer rule has not been made.
     constexpr long long kSimds = 4;
     const long long strips_m = (lx + tlbh::kMomentStrip - 1) / tlbh::kMomentStrip;
     auto rows_for = [&](long long waves) {
